@@ -33,9 +33,7 @@ __global__ __launch_bounds__(256) void l2mix_phi_kernel(int64_t N, int K, const 
 #pragma unroll
     for (int i = 0; i < MAX_TERMS; ++i) {
         if (i < T) {
-            double v = acc[i];
-#pragma unroll
-            for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 16);
+            const double v = lane_sum<16>(acc[i]);
             ll[i] = -v * inv2s2;
             mx = fmax(mx, ll[i]);
         }

@@ -134,20 +134,12 @@ __global__ __launch_bounds__(NT) void propose_kernel(int K, const int32_t* __res
 
 // Log-sum-exp over a particle's 16 lanes, each holding one value (-inf for none).
 __device__ __forceinline__ double lse16(double x) {
-    double mx = x;
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 16));
-    double e = (x > -INFINITY) ? exp(x - mx) : 0.0;
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) e += __shfl_xor(e, off, 16);
+    const double mx = lane_max<16>(x);
+    const double e = lane_sum<16>((x > -INFINITY) ? exp(x - mx) : 0.0);
     return mx + log(e);
 }
 
-__device__ __forceinline__ double sum16(double v) {
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 16);
-    return v;
-}
+__device__ __forceinline__ double sum16(double v) { return lane_sum<16>(v); }
 
 // The same proposal for K <= 128 modes: sixteen lanes per particle (four particles per wave,
 // sixteen per workgroup); a lane draws normal blocks sub, sub + 16, ... and holds the active

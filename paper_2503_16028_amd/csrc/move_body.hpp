@@ -7,12 +7,8 @@ namespace smc {
 
 // Log-sum-exp of each half of the wave, every lane of a half holding one value (-inf for none).
 __device__ __forceinline__ double half_lse(double x) {
-    double mx = x;
-#pragma unroll
-    for (int off = 16; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
-    double e = (x > -INFINITY) ? exp(x - mx) : 0.0;
-#pragma unroll
-    for (int off = 16; off > 0; off >>= 1) e += __shfl_xor(e, off, 64);
+    const double mx = lane_max<32>(x);
+    const double e = lane_sum<32>((x > -INFINITY) ? exp(x - mx) : 0.0);
     return mx + log(e);
 }
 
