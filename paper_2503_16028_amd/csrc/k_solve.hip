@@ -49,11 +49,11 @@ __device__ __forceinline__ f4 mfma_f16(hf8 a, hf8 b, f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
-// The exponent e of |r| = f 2^e, f in [0.5, 1), from rr = |r|^2; clamped, so that a zero or
-// non-finite norm still gives a usable scale.  The transforms take their FP16 input as r 2^-e.
+// The exponent e of |r| = f 2^e, f in [0.5, 1), from rr = |r|^2 = f' 2^k: e = ceil(k / 2); clamped,
+// so that a zero or non-finite norm still gives a usable scale.  The transforms take their FP16
+// input as r 2^-e.
 __device__ __forceinline__ int norm_exponent(double rr) {
-    int ex = 0;
-    (void)frexp(sqrt(rr), &ex);
+    const int ex = (__builtin_amdgcn_frexp_exp(rr) + 1) >> 1;
     return ex < -120 ? -120 : (ex > 120 ? 120 : ex);
 }
 
@@ -68,14 +68,53 @@ struct DstShape {
     static constexpr int TPW = NB * NB / (NW * SP);   // output tiles per wave and strip
     static constexpr int LD = NN + 8;         // 16-bit row stride (16-byte aligned, spreads banks)
     static constexpr int LDZ = NN + 4;        // fp32 row stride of the result
-    static constexpr int BYTES = 2 * NN * LD * 2 + NN * LDZ * 4;
+    // LDS: Z with R^T and T2^T (dead when Z is written) in its first part, then T1 and T3, then the
+    // 1D eigenvalues
+    // (beyond the solver's exchange array too, FP64 up to 64^2)
+    static constexpr int B_AT = NN * LDZ * 4, XCH = (2 * (NN + 1) + NN * NN) * (NN <= 64 ? 8 : 4);
+    static constexpr int LAM_AT = B_AT + NN * LD * 2 > XCH ? B_AT + NN * LD * 2 : (XCH + 15) / 16 * 16;
+    static constexpr int BYTES = LAM_AT + NN * 4;
+    static_assert(NN * LD * 2 <= B_AT, "the first buffer lies inside Z");
     static_assert(NW % NSG == 0 && (NB * NB) % (NW * SP) == 0, "transform tiling");
 };
 
+// A wave's strips of S, held in registers for a whole solve: rows (sg SP + q) 16.. of S (symmetric:
+// also columns, as a B operand), with the eigenvalues of those rows.
+template <int NN, int NW>
+struct DstStrips {
+    using DS = DstShape<NN, NW>;
+    hf8 s[DS::SP][DS::KS];
+    float lam[DS::SP];
+    __device__ __forceinline__ void load(const _Float16* __restrict__ Stab, const float* __restrict__ lamtab, int wave,
+                                         int lane) {
+        const int lr = lane & 15, lk = lane >> 4, sg = wave % DS::NSG;
+#pragma unroll
+        for (int q = 0; q < DS::SP; ++q) {
+            const int row = (sg * DS::SP + q) * 16 + lr;
+#pragma unroll
+            for (int ks = 0; ks < DS::KS; ++ks)
+                s[q][ks] = *reinterpret_cast<const hf8*>(Stab + row * NN + 32 * ks + 8 * lk);
+            lam[q] = lamtab[row];
+        }
+    }
+};
+
+// The eigenvalues into their place in the transform's LDS (read after the transform's first barrier).
+template <int NN, int NW>
+__device__ __forceinline__ void dst_stage_lam(unsigned char* smem, const float* __restrict__ lamtab) {
+    float* lam = reinterpret_cast<float*>(smem + DstShape<NN, NW>::LAM_AT);
+    for (int k = threadIdx.x; k < NN; k += 64 * NW) lam[k] = lamtab[k];
+}
+
+// z = L^{-1} r into Z[g][c] in LDS (at smem), from the thread's strip of r.  Bound by LDS: at 128^2 the
+// four products read 512 KB of operand fragments and the passes between them move another 250 KB
+// (about 6100 clocks at 128 bytes per clock).  So each wave asks for the next tile's fragments before
+// it multiplies this one's (with one tile at a time, every fragment's LDS round trip stood between
+// two products), the eigenvalues come from LDS (from memory they cost a wait per tile of the second
+// product), and the strips of S stay in registers between applications.
 template <typename T, int NN, int R, int NW>
 __device__ __forceinline__ void dst_apply(const T (&rin)[R], double rr, unsigned char* smem,
-                                          const _Float16* __restrict__ Stab, const float* __restrict__ lamtab, int c,
-                                          int b, int wave, int lane) {
+                                          const DstStrips<NN, NW>& S, int c, int b, int wave, int lane) {
     using DS = DstShape<NN, NW>;
     constexpr int LD = DS::LD, LDZ = DS::LDZ, KS = DS::KS, TPW = DS::TPW, SP = DS::SP, NSG = DS::NSG;
     // FP16 operands, FP32 accumulation.  r enters scaled by 2^-e, with |r| = f 2^e and f in
@@ -87,21 +126,12 @@ __device__ __forceinline__ void dst_apply(const T (&rin)[R], double rr, unsigned
     // recover the exact preconditioner's count.
     const int ex = norm_exponent(rr);
     const float sc = ldexpf(1.0f, -ex), unsc = ldexpf(1.0f, ex);
-    _Float16* bufA = reinterpret_cast<_Float16*>(smem);   // R^T, later T2^T
-    _Float16* bufB = bufA + NN * LD;                      // T1, later T3
-    float* Z = reinterpret_cast<float*>(bufB + NN * LD);   // Z[g][c]: lanes of a row read consecutive words
+    _Float16* bufA = reinterpret_cast<_Float16*>(smem);                // R^T, later T2^T
+    _Float16* bufB = reinterpret_cast<_Float16*>(smem + DS::B_AT);     // T1, later T3
+    const float* lamt = reinterpret_cast<const float*>(smem + DS::LAM_AT);
+    float* Z = reinterpret_cast<float*>(smem);   // Z[g][c]: lanes of a row read consecutive words
     const int lr = lane & 15, lk = lane >> 4;
-    const int sg = wave % NSG, wq = wave / NSG;
-    hf8 sfrag[SP][KS];   // rows (sg SP + s) 16.. of S (symmetric: also columns, as a B operand)
-    float lam_col[SP];
-#pragma unroll
-    for (int q = 0; q < SP; ++q) {
-        const int sb = sg * SP + q;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            sfrag[q][ks] = *reinterpret_cast<const hf8*>(Stab + (sb * 16 + lr) * NN + 32 * ks + 8 * lk);
-        lam_col[q] = lamtab[sb * 16 + lr];
-    }
+    const int sg = wave % NSG, t0 = (wave / NSG) * TPW;   // the wave's strips of S and its first data tile
     {   // stage R^T[c][g] = fp16(r 2^-e): the thread's strip is contiguous
         _Float16* dst = bufA + c * LD + b * R;
         if constexpr (R % 8 == 0) {
@@ -121,87 +151,61 @@ __device__ __forceinline__ void dst_apply(const T (&rin)[R], double rr, unsigned
     // Each product is ordered so that the four values a lane holds in its 16 x 16 result tile
     // are consecutive in the layout the next product reads (one 8-byte or 16-byte store per tile),
     // while both operands stay contiguous along the contraction index.
-#pragma unroll 1
-    for (int tt = 0; tt < TPW; ++tt) {   // T1[k][c] = sum_g S[k][g] R[g][c], as (R^T S)[c][k]
-        const int cb = wq * TPW + tt;
-        f4 acc[SP];
+    hf8 av[2][KS];
+    auto fetch = [&](const _Float16* in, int tt) __attribute__((always_inline)) {
+        const _Float16* at = in + ((t0 + tt) * 16 + lr) * LD + 8 * lk;
 #pragma unroll
-        for (int q = 0; q < SP; ++q) acc[q] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int ks = 0; ks < KS; ++ks) av[tt & 1][ks] = *reinterpret_cast<const hf8*>(at + 32 * ks);
+    };
+    // one product: P = in S (16 rows of `in` per data tile), or its transpose when LAST
+    auto product = [&](const _Float16* in, auto last, auto store) __attribute__((always_inline)) {
+        constexpr bool LAST = decltype(last)::value;
+        fetch(in, 0);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const hf8 av = *reinterpret_cast<const hf8*>(bufA + (cb * 16 + lr) * LD + 32 * ks + 8 * lk);
+        for (int tt = 0; tt < TPW; ++tt) {
+            if (tt + 1 < TPW) fetch(in, tt + 1);
+            __builtin_amdgcn_sched_barrier(0);   // the fetch above goes out before the products below
+            f4 acc[SP];
 #pragma unroll
-            for (int q = 0; q < SP; ++q) acc[q] = mfma_f16(av, sfrag[q][ks], acc[q]);
+            for (int q = 0; q < SP; ++q) acc[q] = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int q = 0; q < SP; ++q)
+                    acc[q] = LAST ? mfma_f16(S.s[q][ks], av[tt & 1][ks], acc[q])
+                                  : mfma_f16(av[tt & 1][ks], S.s[q][ks], acc[q]);
+#pragma unroll
+            for (int q = 0; q < SP; ++q) store(t0 + tt, q, acc[q]);
         }
-#pragma unroll
-        for (int q = 0; q < SP; ++q) {
+    };
+    auto put = [&](_Float16* out) {
+        return [=](int tile, int q, f4 acc) __attribute__((always_inline)) {
             hf4 o;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) o[v] = (_Float16)acc[q][v];
-            *reinterpret_cast<hf4*>(bufB + ((sg * SP + q) * 16 + lr) * LD + cb * 16 + 4 * lk) = o;
-        }
-    }
+            for (int v = 0; v < 4; ++v) o[v] = (_Float16)acc[v];
+            *reinterpret_cast<hf4*>(out + ((sg * SP + q) * 16 + lr) * LD + tile * 16 + 4 * lk) = o;
+        };
+    };
+    // T1[k][c] = sum_g S[k][g] R[g][c], as (R^T S)[c][k]
+    product(bufA, std::false_type{}, put(bufB));
     __syncthreads();
-#pragma unroll 1
-    for (int tt = 0; tt < TPW; ++tt) {   // T2^T[l][k] = (sum_c T1[k][c] S[c][l]) / (lam_k + lam_l)
-        const int rb = wq * TPW + tt;
-        f4 acc[SP];
+    // T2^T[l][k] = (sum_c T1[k][c] S[c][l]) / (lam_k + lam_l)
+    product(bufB, std::false_type{}, [&](int tile, int q, f4 acc) __attribute__((always_inline)) {
+        const f4 lk4 = *reinterpret_cast<const f4*>(lamt + tile * 16 + 4 * lk);
+        f4 w;
 #pragma unroll
-        for (int q = 0; q < SP; ++q) acc[q] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const hf8 av = *reinterpret_cast<const hf8*>(bufB + (rb * 16 + lr) * LD + 32 * ks + 8 * lk);
-#pragma unroll
-            for (int q = 0; q < SP; ++q) acc[q] = mfma_f16(av, sfrag[q][ks], acc[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < SP; ++q) {
-            hf4 o;
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                o[v] = (_Float16)(acc[q][v] * __builtin_amdgcn_rcpf(lamtab[rb * 16 + 4 * lk + v] + lam_col[q]));
-            *reinterpret_cast<hf4*>(bufA + ((sg * SP + q) * 16 + lr) * LD + rb * 16 + 4 * lk) = o;
-        }
-    }
+        for (int v = 0; v < 4; ++v) w[v] = acc[v] * __builtin_amdgcn_rcpf(lk4[v] + S.lam[q]);
+        put(bufA)(tile, q, w);
+    });
     __syncthreads();
-#pragma unroll 1
-    for (int tt = 0; tt < TPW; ++tt) {   // T3[g][l] = sum_k S[g][k] T2[k][l], as (T2^T S)[l][g]
-        const int cb = wq * TPW + tt;
-        f4 acc[SP];
-#pragma unroll
-        for (int q = 0; q < SP; ++q) acc[q] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const hf8 av = *reinterpret_cast<const hf8*>(bufA + (cb * 16 + lr) * LD + 32 * ks + 8 * lk);
-#pragma unroll
-            for (int q = 0; q < SP; ++q) acc[q] = mfma_f16(av, sfrag[q][ks], acc[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < SP; ++q) {
-            hf4 o;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) o[v] = (_Float16)acc[q][v];
-            *reinterpret_cast<hf4*>(bufB + ((sg * SP + q) * 16 + lr) * LD + cb * 16 + 4 * lk) = o;
-        }
-    }
+    // T3[g][l] = sum_k S[g][k] T2[k][l], as (T2^T S)[l][g]
+    product(bufA, std::false_type{}, put(bufB));
     __syncthreads();
-#pragma unroll 1
-    for (int tt = 0; tt < TPW; ++tt) {   // Z[g][c] = sum_l T3[g][l] S[l][c], as (S T3^T)[c][g]
-        const int rb = wq * TPW + tt;
-        f4 acc[SP];
-#pragma unroll
-        for (int q = 0; q < SP; ++q) acc[q] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const hf8 bv = *reinterpret_cast<const hf8*>(bufB + (rb * 16 + lr) * LD + 32 * ks + 8 * lk);
-#pragma unroll
-            for (int q = 0; q < SP; ++q) acc[q] = mfma_f16(sfrag[q][ks], bv, acc[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < SP; ++q)
-            *reinterpret_cast<float4*>(Z + (rb * 16 + lr) * LDZ + (sg * SP + q) * 16 + 4 * lk) =
-                make_float4(acc[q][0] * unsc, acc[q][1] * unsc, acc[q][2] * unsc, acc[q][3] * unsc);
-    }
+    // Z[g][c] = sum_l T3[g][l] S[l][c], as (S T3^T)[c][g]
+    product(bufB, std::true_type{}, [&](int tile, int q, f4 acc) __attribute__((always_inline)) {
+        *reinterpret_cast<float4*>(Z + (tile * 16 + lr) * LDZ + (sg * SP + q) * 16 + 4 * lk) =
+            make_float4(acc[0] * unsc, acc[1] * unsc, acc[2] * unsc, acc[3] * unsc);
+    });
     __syncthreads();
 }
 
@@ -223,9 +227,12 @@ __global__ __launch_bounds__(NN * NN / R) void dst_apply_kernel(const float* __r
         r[k] = rin[base + (b * R + k) * NN + c];
         acc += (double)r[k] * (double)r[k];
     }
+    DstStrips<NN, NW> S;
+    S.load(Stab, lamtab, tid >> 6, tid & 63);
+    dst_stage_lam<NN, NW>(smem, lamtab);
     const double rr = block_sum<NW>(acc, red);
-    dst_apply<float, NN, R, NW>(r, rr, smem, Stab, lamtab, c, b, tid >> 6, tid & 63);
-    const float* Z = reinterpret_cast<const float*>(smem + 2 * NN * DstShape<NN, NW>::LD * 2);
+    dst_apply<float, NN, R, NW>(r, rr, smem, S, c, b, tid >> 6, tid & 63);
+    const float* Z = reinterpret_cast<const float*>(smem);
 #pragma unroll
     for (int k = 0; k < R; ++k) zout[base + (b * R + k) * NN + c] = Z[(b * R + k) * DstShape<NN, NW>::LDZ + c];
 }
@@ -626,6 +633,7 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
     constexpr int NW = NT / 64;
     constexpr int NP1 = NN + 1;
     constexpr int PAD = NN + 1;
+    constexpr int XBYTES = (2 * PAD + NN * NN) * (int)sizeof(T);
     using DS = DstShape<NN, NW>;
     static_assert(!DST || NN >= 32, "transform tiling");
     static_assert(NW <= 16, "reduction slots");
@@ -684,17 +692,24 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
     for (int r = 0; r < R; ++r) t[r] = tb[NN + 1 + r * NN];
     __syncthreads();
 
+    // the transform's strips of S in registers and its eigenvalues in LDS, beyond the exchange array
+    static_assert(!DST || XBYTES <= DS::LAM_AT, "the exchange array keeps off the eigenvalues");
+    DstStrips<NN, NW> strips;
+    if constexpr (DST) {
+        strips.load(Stab, lamtab, wave, lane);
+        dst_stage_lam<NN, NW>(smem, lamtab);
+    }
     // z = L^{-1} r into Z[g][c] (LDS), with the barriers of the four products
     int napp = 0;   // preconditioner applications (same in every thread)
     auto precondition = [&](const T (&rin)[R], double rrin) __attribute__((always_inline)) {
         if constexpr (DST) {
-            dst_apply<T, NN, R, NW>(rin, rrin, smem, Stab, lamtab, c, b, wave, lane);
+            dst_apply<T, NN, R, NW>(rin, rrin, smem, strips, c, b, wave, lane);
             ++napp;
         }
     };
     auto zval = [&](int r) __attribute__((always_inline)) -> T {
         if constexpr (DST) {
-            const float* Z = reinterpret_cast<const float*>(smem + 2 * NN * DS::LD * 2);
+            const float* Z = reinterpret_cast<const float*>(smem);
             return (T)Z[(b * R + r) * DS::LDZ + c];
         } else {
             return T(0);
@@ -951,7 +966,7 @@ constexpr int D256_BYTES = 256 * D256_LD * 2;
 // LDS named at module level: the mixed-grid solve's bodies and the 256^2 transform below are
 // functions of their own (register-allocated apart from their callers), and LDS they name directly
 // keeps its LDS instructions, where a pointer passed in would turn into generic accesses.
-constexpr int MIXED_SMEM = cmax(onchip_smem<float, 128, 16, true>(),
+constexpr int MIXED_SMEM = cmax(cmax(D256_BYTES, onchip_smem<float, 128, 16, true>()),
                                 cmax(onchip_smem<float, 64, 4, true>(), onchip_smem<double, 64, 4, false>()));
 __shared__ __align__(16) unsigned char g_mixed_smem[MIXED_SMEM];
 
