@@ -563,6 +563,7 @@ static hipError_t forward(smc_problem_s* ps, int level, int prec, int64_t N, con
     }
     a.fwd_given = o.w_given ? 1 : 0;
     a.lam = o.adjoint ? P.ws_lam : nullptr;
+    a.keep = o.w || o.adjoint;
     a.stats = P.profiling ? P.stats : nullptr;
     // the on-chip FP32 solvers form dPhi/du after the adjoint solve, into the scaling rows (free once
     // the solve is done); the gradient then only contracts it (see du_formed)

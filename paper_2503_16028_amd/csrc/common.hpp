@@ -177,8 +177,8 @@ __device__ __forceinline__ double uniform(double v) {
 
 // Sum over the block in a fixed order; every thread gets the same bits (and the compiler knows).
 // `red` holds at least NW doubles of LDS; contains a barrier.
-template <int NW>
-__device__ __forceinline__ double block_sum(double v, double* red) {
+template <int NW, typename P>
+__device__ __forceinline__ double block_sum(double v, P red) {
     v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
@@ -197,6 +197,8 @@ struct SolveArgs {
     int64_t e_stride, x_stride, sd_stride, vec_stride;
     double* lam;         // adjoint solution [N][lam_stride] (interior layout as x64), or null: no adjoint
     int64_t lam_stride;
+    int keep;            // the whole FP64 solution is wanted in x64 (on-chip solvers may else form only
+                         // the observations and use x64's row as they like)
     int fwd_given;       // x64 already holds the forward solution: only the adjoint problem is solved
     int64_t row0;        // first particle row
     const int32_t* obs;  // [n_obs] nodal flat index

@@ -68,12 +68,8 @@ struct DstShape {
     static constexpr int TPW = NB * NB / (NW * SP);   // output tiles per wave and strip
     static constexpr int LD = NN + 8;         // 16-bit row stride (16-byte aligned, spreads banks)
     static constexpr int LDZ = NN + 4;        // fp32 row stride of the result
-    // LDS: Z with R^T and T2^T (dead when Z is written) in its first part, then T1 and T3, then the
-    // 1D eigenvalues
-    // (beyond the solver's exchange array too, FP64 up to 64^2)
-    static constexpr int B_AT = NN * LDZ * 4, XCH = (2 * (NN + 1) + NN * NN) * (NN <= 64 ? 8 : 4);
-    static constexpr int LAM_AT = B_AT + NN * LD * 2 > XCH ? B_AT + NN * LD * 2 : (XCH + 15) / 16 * 16;
-    static constexpr int BYTES = LAM_AT + NN * 4;
+    // LDS: Z with R^T and T2^T (dead when Z is written) in its first part, then T1 and T3
+    static constexpr int B_AT = NN * LDZ * 4, BYTES = B_AT + NN * LD * 2;
     static_assert(NN * LD * 2 <= B_AT, "the first buffer lies inside Z");
     static_assert(NW % NSG == 0 && (NB * NB) % (NW * SP) == 0, "transform tiling");
 };
@@ -99,10 +95,9 @@ struct DstStrips {
     }
 };
 
-// The eigenvalues into their place in the transform's LDS (read after the transform's first barrier).
+// The eigenvalues into LDS (read after the transform's first barrier).
 template <int NN, int NW>
-__device__ __forceinline__ void dst_stage_lam(unsigned char* smem, const float* __restrict__ lamtab) {
-    float* lam = reinterpret_cast<float*>(smem + DstShape<NN, NW>::LAM_AT);
+__device__ __forceinline__ void dst_stage_lam(float* lam, const float* __restrict__ lamtab) {
     for (int k = threadIdx.x; k < NN; k += 64 * NW) lam[k] = lamtab[k];
 }
 
@@ -113,7 +108,7 @@ __device__ __forceinline__ void dst_stage_lam(unsigned char* smem, const float* 
 // two products), the eigenvalues come from LDS (from memory they cost a wait per tile of the second
 // product), and the strips of S stay in registers between applications.
 template <typename T, int NN, int R, int NW>
-__device__ __forceinline__ void dst_apply(const T (&rin)[R], double rr, unsigned char* smem,
+__device__ __forceinline__ void dst_apply(const T (&rin)[R], double rr, unsigned char* smem, const float* lamt,
                                           const DstStrips<NN, NW>& S, int c, int b, int wave, int lane) {
     using DS = DstShape<NN, NW>;
     constexpr int LD = DS::LD, LDZ = DS::LDZ, KS = DS::KS, TPW = DS::TPW, SP = DS::SP, NSG = DS::NSG;
@@ -128,7 +123,6 @@ __device__ __forceinline__ void dst_apply(const T (&rin)[R], double rr, unsigned
     const float sc = ldexpf(1.0f, -ex), unsc = ldexpf(1.0f, ex);
     _Float16* bufA = reinterpret_cast<_Float16*>(smem);                // R^T, later T2^T
     _Float16* bufB = reinterpret_cast<_Float16*>(smem + DS::B_AT);     // T1, later T3
-    const float* lamt = reinterpret_cast<const float*>(smem + DS::LAM_AT);
     float* Z = reinterpret_cast<float*>(smem);   // Z[g][c]: lanes of a row read consecutive words
     const int lr = lane & 15, lk = lane >> 4;
     const int sg = wave % NSG, t0 = (wave / NSG) * TPW;   // the wave's strips of S and its first data tile
@@ -216,7 +210,7 @@ __global__ __launch_bounds__(NN * NN / R) void dst_apply_kernel(const float* __r
                                                                const _Float16* __restrict__ Stab,
                                                                const float* __restrict__ lamtab) {
     constexpr int NT = NN * NN / R, NW = NT / 64;
-    __shared__ __align__(16) unsigned char smem[DstShape<NN, NW>::BYTES];
+    __shared__ __align__(16) unsigned char smem[DstShape<NN, NW>::BYTES + NN * 4];
     __shared__ double red[16];
     const int tid = threadIdx.x, c = tid % NN, b = tid / NN;
     const int64_t base = (int64_t)blockIdx.x * NN * NN;
@@ -229,9 +223,10 @@ __global__ __launch_bounds__(NN * NN / R) void dst_apply_kernel(const float* __r
     }
     DstStrips<NN, NW> S;
     S.load(Stab, lamtab, tid >> 6, tid & 63);
-    dst_stage_lam<NN, NW>(smem, lamtab);
+    float* lamt = reinterpret_cast<float*>(smem + DstShape<NN, NW>::BYTES);
+    dst_stage_lam<NN, NW>(lamt, lamtab);
     const double rr = block_sum<NW>(acc, red);
-    dst_apply<float, NN, R, NW>(r, rr, smem, S, c, b, tid >> 6, tid & 63);
+    dst_apply<float, NN, R, NW>(r, rr, smem, lamt, S, c, b, tid >> 6, tid & 63);
     const float* Z = reinterpret_cast<const float*>(smem);
 #pragma unroll
     for (int k = 0; k < R; ++k) zout[base + (b * R + k) * NN + c] = Z[(b * R + k) * DstShape<NN, NW>::LDZ + c];
@@ -257,12 +252,18 @@ hipError_t launch_dst_apply(int n, int64_t N, const float* r, float* z, const vo
 
 constexpr int cmax(int x, int y) { return x > y ? x : y; }
 
-// LDS bytes of the on-chip solver's big buffer: the exchange array, or the transform buffers.
-template <typename T, int NN, int R, bool DST>
+// LDS of the on-chip solver's big buffer: the exchange array and, when the iterate is not kept, the
+// scaled residuals behind it; the transform buffers over both; then (DST) the eigenvalues.
+template <typename T, int NN>
+constexpr int onchip_out_at() { return ((2 * (NN + 1) + NN * NN) * (int)sizeof(T) + 15) / 16 * 16; }
+template <typename T, int NN, int NW, bool KEEP>
+constexpr int onchip_lam_at() {
+    return cmax(onchip_out_at<T, NN>() + (KEEP ? 0 : NN * NN * (int)sizeof(T)), DstShape<NN, NW>::BYTES);
+}
+template <typename T, int NN, int R, bool DST, bool KEEP = true>
 constexpr int onchip_smem() {
-    constexpr int NW = NN * NN / R / 64;
-    constexpr int XBYTES = (2 * (NN + 1) + NN * NN) * (int)sizeof(T);
-    return (DST && DstShape<NN, NW>::BYTES > XBYTES) ? DstShape<NN, NW>::BYTES : XBYTES;
+    if constexpr (DST) return onchip_lam_at<T, NN, NN * NN / R / 64, KEEP>() + NN * 4;
+    else return onchip_out_at<T, NN>();
 }
 
 // Small LDS of one solve: block-reduction slots and the adjoint's point sources.
@@ -326,6 +327,17 @@ __device__ __forceinline__ double from_prev_lane(double v, double edge) {
     const int hi = __builtin_amdgcn_update_dpp((int)(be >> 32), (int)(b >> 32), 0x138, 0xF, 0xF, false);
     return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
+
+// Element at a 32-bit byte offset from a wave-uniform base: the base then sits in SGPRs and a lane
+// holds one offset for a whole block of rows (rows a constant distance apart fold into the
+// instruction), where per-lane 64-bit pointers took two registers per load in flight.
+typedef const __attribute__((address_space(1))) char* gcbp;
+typedef __attribute__((address_space(1))) char* gbp;
+__device__ __forceinline__ gcbp uniform_base(const void* p) { return (gcbp)wave_uniform((const double*)p); }
+template <typename S>
+__device__ __forceinline__ S at_off(gcbp base, uint32_t off) { return *(gcp<S>)(base + off); }
+template <typename S>
+__device__ __forceinline__ void put_off(gcbp base, uint32_t off, S v) { *(gp<S>)((gbp)base + off) = v; }
 
 // Scaled residual D^{-1/2} (f - A x) of the strip into its LDS slots (x = 0 when `zero_x`);
 // returns the sum of squares of the unscaled residual.  Every load has a clamped, in-bounds index
@@ -482,6 +494,124 @@ __device__ __noinline__ void strip_update(double* xo_, const SD* sd_, const T* t
     }
 }
 
+// One refinement step of the forward problem when only its observations are wanted: with the inner
+// solution y in the strip's LDS slots, the correction dx = D^{-1/2} y is rounded to T and staged, the
+// FP64 residual in `rb` is updated, r <- r - A dx (r = f before the first step), and the scaled
+// residual D^{-1/2} r goes to the strip's `out` slots (an LDS array of its own: other waves still read
+// dx).  Returns the strip's share of |r|^2.  The iterate itself is never formed: dx is exact as stored, the update evaluates
+// the same FP64 operator as strip_residual, so r = f - A (sum of dx) up to FP64 rounding, and each
+// observation is the FP64 sum of its node's corrections (g_src_at: the nodes, g_src_w: the sums).
+// Bound by its memory instructions and the chain from loads to stores: per node and step it reads e, r
+// and D^{-1/2} and writes r, where a separate iterate read and wrote x, read it again with its
+// neighbours, and passed twice; the neighbours of dx are LDS words at immediate offsets.  Measured with
+// the reciprocal root of the setup: a 20-move stage of 4096 particles at 128^2 48.6 -> 42.3 ms, of 1024
+// at 64^2 in FP64 3.91 -> 3.34 ms, the potentials of 8 particles at 128^2 143 -> 120 us.
+template <typename T, int NN, int R, typename SD, bool SE = true>
+__device__ __forceinline__ double strip_refine(const double* __restrict__ e_, double* __restrict__ rb_,
+                                            const SD* __restrict__ sd_, T* ly_, T* out_, int c, int g0, bool first,
+                                            double f, int n_obs) {
+    constexpr int NP1 = NN + 1, PAD = NN + 1, NT = NN * NN / R;
+    constexpr bool WIDE = NN % 64 == 0;   // a wave covers consecutive columns of one row
+    const double n2 = (double)NN * (double)NN;
+    const gcbp e = uniform_base(e_), rb = uniform_base(rb_), sd = uniform_base(sd_);
+    typedef __attribute__((address_space(3))) T* ltp;
+    ltp ly = (ltp)ly_;
+    ltp tb = ly + PAD + g0 * NN + c;      // own node of row r at tb[r NN]
+    ltp out = (ltp)out_ + g0 * NN + c;    // and its scaled residual
+    const int i = c + 1, tid = threadIdx.x, lane = tid & 63;
+    const bool colin = c < NN - 1;
+    constexpr int B = R < 8 ? R : 8;   // rows whose loads are issued together
+    static_assert(R % B == 0, "strip blocking");
+    const uint32_t own = (uint32_t)(g0 * NN + c), eown = (uint32_t)((g0 + 1) * NP1 + i) * 8u;
+#pragma unroll 1
+    for (int r0 = 0; r0 < R; r0 += B) {
+        const uint32_t at = (own + (uint32_t)(r0 * NN)) * (uint32_t)sizeof(SD);
+        SD sv[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) sv[k] = at_off<SD>(sd, at + k * NN * (uint32_t)sizeof(SD));
+#pragma unroll
+        for (int k = 0; k < B; ++k) tb[(r0 + k) * NN] = (T)sv[k] * tb[(r0 + k) * NN];
+    }
+    for (int k = tid; k < PAD; k += NT) {   // rows -1 and NN, and column -1, of the exchange array
+        ly[k] = T(0);
+        ly[PAD + NN * NN + k] = T(0);
+    }
+    const int c0 = WIDE ? __builtin_amdgcn_readfirstlane(c - lane) : 0;   // first column of the wave
+    const int ieE = min(c0 + 65, NN), ieW = c0;                            // e columns beyond the wave's edges
+    kcdp eu = (kcdp)wave_uniform(e_);
+    const int g0u = __builtin_amdgcn_readfirstlane(g0);
+    double eS = at_off<double>(e, eown - NP1 * 8u), eC = at_off<double>(e, eown);
+    __syncthreads();
+    if (tid < n_obs) {
+        const int at = g_src_at[tid];
+        if (at >= 0) g_src_w[tid] += (double)ly[PAD + at];
+    }
+    double dS = (double)tb[-NN], dC = (double)tb[0];
+    double acc = 0.0;
+#pragma unroll 1
+    for (int r0 = 0; r0 < R; r0 += B) {
+        const uint32_t at = own + (uint32_t)(r0 * NN), eat = eown + (uint32_t)(r0 * NP1) * 8u;
+        double eN[B], ro[B], eEe[B], eWe[B];
+        SD sv[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            // row j + 1 of e; only a strip's last row can be row n + 1, and reads row n instead
+            const uint32_t up = k + 1 < B || g0 + r0 + B < NN ? NP1 * 8u : 0u;
+            eN[k] = at_off<double>(e, eat + k * NP1 * 8u + up);
+            sv[k] = at_off<SD>(sd, (at + k * NN) * (uint32_t)sizeof(SD));
+            if constexpr (WIDE) {
+                const int ju = g0u + r0 + k + 1;
+                eEe[k] = SE ? eu[ju * NP1 + ieE] : at_off<double>(e, (uint32_t)(ju * NP1 + ieE) * 8u);
+                eWe[k] = SE ? eu[ju * NP1 + ieW] : at_off<double>(e, (uint32_t)(ju * NP1 + ieW) * 8u);
+            } else {
+                eEe[k] = at_off<double>(e, eat + k * NP1 * 8u + (i < NN ? 8u : 0u));
+                eWe[k] = at_off<double>(e, eat + k * NP1 * 8u - 8u);
+            }
+            ro[k] = f;
+        }
+        if (!first) {
+#pragma unroll
+            for (int k = 0; k < B; ++k) ro[k] = at_off<double>(rb, (at + k * NN) * 8u);
+        }
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const int r = r0 + k;
+            const double eE = WIDE ? from_next_lane(eC, eEe[k]) : eEe[k];
+            const double eW = WIDE ? from_prev_lane(eC, eWe[k]) : eWe[k];
+            const double dE = (double)tb[r * NN + 1], dW = (double)tb[r * NN - 1], dN = (double)tb[(r + 1) * NN];
+            const double flux = eE * (dC - dE) + eW * (dC - dW) + eN[k] * (dC - dN) + eS * (dC - dS);
+            const bool in = colin && g0 + r < NN - 1;
+            const double res = in ? ro[k] - eC * n2 * flux : 0.0;
+            put_off<double>(rb, (at + k * NN) * 8u, res);
+            acc += res * res;
+            out[r * NN] = (T)((double)sv[k] * res);
+            eS = eC;
+            eC = eN[k];
+            dS = dC;
+            dC = dN;
+        }
+    }
+    return acc;
+}
+
+// The first scaled residual D^{-1/2} f into the strip's `out` slots.
+template <typename T, int NN, int R, typename SD>
+__device__ __forceinline__ void strip_first(const SD* __restrict__ sd_, T* out_, int c, int g0, double f) {
+    const gcbp sd = uniform_base(sd_);
+    __attribute__((address_space(3))) T* out = (__attribute__((address_space(3))) T*)out_ + g0 * NN + c;
+    constexpr int B = R < 16 ? R : 16;
+#pragma unroll 1
+    for (int r0 = 0; r0 < R; r0 += B) {
+        const uint32_t at = (uint32_t)((g0 + r0) * NN + c) * (uint32_t)sizeof(SD);
+        SD sv[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) sv[k] = at_off<SD>(sd, at + k * NN * (uint32_t)sizeof(SD));
+#pragma unroll
+        for (int k = 0; k < B; ++k)
+            out[(r0 + k) * NN] = (c < NN - 1 && g0 + r0 + k < NN - 1) ? (T)((double)sv[k] * f) : T(0);
+    }
+}
+
 // dPhi/du at the strip's nodes after the forward solution w and the adjoint solution lam are final
 // (App. B's gradient of the discrete potential, the derivative of the face coefficient a_PQ = e_P e_Q
 // by u_P being a_PQ / 2):
@@ -572,16 +702,25 @@ __device__ __noinline__ void strip_dphi(const double* __restrict__ e_, const dou
     }
 }
 
+// 1 / sqrt(x) for a positive normal x: the hardware estimate y, then one third-order step
+// y (1 + d / 2 + 3 d^2 / 8), d = 1 - x y^2 (the binomial series; d^3 is below FP64's rounding).  The
+// setup needs one such root per node: the library's square root and divide are about 40 FP64
+// instructions in a chain, this is six.
+__device__ __forceinline__ double rsqrt64(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double d = __builtin_fma(-x * y, y, 1.0);
+    return __builtin_fma(y * d, __builtin_fma(0.375, d, 0.5), y);
+}
+
 // D^{-1/2} into the workspace and t = sqrt(e_P / sum e_Q) into the strip's LDS slots (SE as for
 // strip_residual).
 template <typename T, int NN, int R, typename SD, bool SE = true>
-__device__ __noinline__ void strip_setup(const double* __restrict__ e_, SD* __restrict__ sd_, T* __restrict__ tb_,
+__device__ __forceinline__ void strip_setup(const double* __restrict__ e_, SD* __restrict__ sd_, T* __restrict__ tb_,
                                          int c, int g0) {
     static_assert(NN % 64 == 0, "a wave covers consecutive columns of one row");
     constexpr int NP1 = NN + 1;
     const double h = 1.0 / NN;
-    gcdp e = (gcdp)e_;
-    gp<SD> sd = (gp<SD>)sd_;
+    const gcbp e = uniform_base(e_), sd = uniform_base(sd_);
     __attribute__((address_space(3))) T* tb = (__attribute__((address_space(3))) T*)tb_;
     const int i = c + 1;
     const int lane = threadIdx.x & 63;
@@ -589,41 +728,67 @@ __device__ __noinline__ void strip_setup(const double* __restrict__ e_, SD* __re
     const int ieE = min(c0 + 65, NN), ieW = c0;
     kcdp eu = (kcdp)wave_uniform(e_);
     const int g0u = __builtin_amdgcn_readfirstlane(g0);
-    double eS = e[g0 * NP1 + i], eC = e[(g0 + 1) * NP1 + i];
+    const uint32_t own = (uint32_t)(g0 * NN + c), eown = (uint32_t)((g0 + 1) * NP1 + i) * 8u;
+    double eS = at_off<double>(e, eown - NP1 * 8u), eC = at_off<double>(e, eown);
     constexpr int B = R < 16 ? R : 16;
 #pragma unroll 1
     for (int r0 = 0; r0 < R; r0 += B) {
+        const uint32_t at = own + (uint32_t)(r0 * NN), eat = eown + (uint32_t)(r0 * NP1) * 8u;
         double eN[B], eEe[B], eWe[B];
 #pragma unroll
         for (int k = 0; k < B; ++k) {
-            const int j = g0 + r0 + k + 1, ju = g0u + r0 + k + 1;
-            eN[k] = e[min(j + 1, NN) * NP1 + i];
-            eEe[k] = SE ? eu[ju * NP1 + ieE] : e[ju * NP1 + ieE];
-            eWe[k] = SE ? eu[ju * NP1 + ieW] : e[ju * NP1 + ieW];
+            const uint32_t up = k + 1 < B || g0 + r0 + B < NN ? NP1 * 8u : 0u;   // never past row n
+            const int ju = g0u + r0 + k + 1;
+            eN[k] = at_off<double>(e, eat + k * NP1 * 8u + up);
+            eEe[k] = SE ? eu[ju * NP1 + ieE] : at_off<double>(e, (uint32_t)(ju * NP1 + ieE) * 8u);
+            eWe[k] = SE ? eu[ju * NP1 + ieW] : at_off<double>(e, (uint32_t)(ju * NP1 + ieW) * 8u);
         }
 #pragma unroll
         for (int k = 0; k < B; ++k) {
-            const int r = r0 + k, g = g0 + r, j = g + 1;
+            const int r = r0 + k, g = g0 + r;
             const bool in = c < NN - 1 && g < NN - 1;
             const double S = from_next_lane(eC, eEe[k]) + from_prev_lane(eC, eWe[k]) + eN[k] + eS;
-            const double rs = 1.0 / sqrt(eC * S);   // h / sqrt(eC S) and sqrt(eC / S) from one root
-            sd[g * NN + c] = in ? (SD)(h * rs) : SD(1);
+            const double rs = rsqrt64(eC * S);   // h / sqrt(eC S) and sqrt(eC / S) from one root
+            put_off<SD>(sd, (at + k * NN) * (uint32_t)sizeof(SD), in ? (SD)(h * rs) : SD(1));
             tb[NN + 1 + r * NN] = in ? (T)(eC * rs) : T(0);
             eS = eC;
-            eC = (j + 1 <= NN) ? eN[k] : 0.0;
+            eC = eN[k];
         }
     }
 }
 
+// The same out of line.  A wide strip's pass unrolls over many rows and would take its registers from
+// the conjugate-gradient loop; a narrow one (eight rows and fewer) is small, and inline the kernel's own
+// register limit holds for it too (out of line it took 132 registers at 64^2: one workgroup per
+// compute unit where two fit).
+template <typename T, int NN, int R, typename SD, bool SE>
+__device__ __noinline__ double strip_refine_call(const double* __restrict__ e, double* __restrict__ rb,
+                                                 const SD* __restrict__ sd, T* ly, T* out, int c, int g0, bool first,
+                                                 double f, int n_obs) {
+    return strip_refine<T, NN, R, SD, SE>(e, rb, sd, ly, out, c, g0, first, f, n_obs);
+}
+template <typename T, int NN, int R, typename SD>
+__device__ __noinline__ void strip_first_call(const SD* __restrict__ sd, T* out, int c, int g0, double f) {
+    strip_first<T, NN, R, SD>(sd, out, c, g0, f);
+}
+template <typename T, int NN, int R, typename SD, bool SE>
+__device__ __noinline__ void strip_setup_call(const double* __restrict__ e, SD* __restrict__ sd, T* __restrict__ tb,
+                                              int c, int g0) {
+    strip_setup<T, NN, R, SD, SE>(e, sd, tb, c, g0);
+}
+
 // One particle's solve by the whole workgroup (NN * NN / R threads); `smem` holds at least
 // onchip_smem<T, NN, R, DST>() bytes.  Used by the per-grid kernel and by the mixed-grid one.
-template <typename T, int NN, int R, bool DST, bool ADJ, bool SE = true, bool AONLY = false>
+// KEEP: the FP64 solution is wanted whole (the caller's forward state, or the adjoint solve that
+// follows); otherwise only its observations are formed and x64's row holds the FP64 residual.
+template <typename T, int NN, int R, bool DST, bool ADJ, bool SE = true, bool AONLY = false, bool KEEP = true>
 __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t row, const int32_t* __restrict__ obs,
                                                unsigned char* smem, SolveShared& sh,
                                                const _Float16* __restrict__ Stab, const float* __restrict__ lamtab) {
     // AONLY: the adjoint problem alone, the forward solution already in x64 from an earlier launch
     // (whose iteration count, or -1 for a failed solve, is in iters unless the caller gave w)
     static_assert(!AONLY || ADJ, "adjoint-only needs the adjoint pass");
+    static_assert(KEEP || (DST && !ADJ), "the adjoint pass reads the whole forward solution");
     int prev_iters = 0;
     if constexpr (AONLY) {
         prev_iters = (a.iters && !a.fwd_given) ? __builtin_amdgcn_readfirstlane(a.iters[row]) : 0;
@@ -633,12 +798,12 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
     constexpr int NW = NT / 64;
     constexpr int NP1 = NN + 1;
     constexpr int PAD = NN + 1;
-    constexpr int XBYTES = (2 * PAD + NN * NN) * (int)sizeof(T);
+    constexpr int OUT_AT = onchip_out_at<T, NN>();
     using DS = DstShape<NN, NW>;
     static_assert(!DST || NN >= 32, "transform tiling");
     static_assert(NW <= 16, "reduction slots");
-    // FP64 passes as separate, unrolled functions (wide strips); inline loops otherwise
-    constexpr bool SPLIT = R >= 32;
+    // FP64 passes as separate, unrolled functions (rows of whole waves); inline loops otherwise
+    constexpr bool SPLIT = NN % 64 == 0 && DST, WIDE = R >= 16;
     double* red1 = sh.red1;
     double* red2 = sh.red2;
     double* src_w = g_src_w;   // module-level: the residual function reads them by name
@@ -659,6 +824,7 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
     const double h = 1.0 / NN, inv_h2 = (double)NN * (double)NN;
     // own node of row r: tb[NN + 1 + r * NN]; east +1, west -1, north +NN, south -NN
     T* tb = ly + PAD + b * R * NN + c - NN - 1;
+    T* lout = reinterpret_cast<T*>(smem + OUT_AT);   // scaled residuals [g][c] (not KEEP)
 
     for (int k = tid; k < PAD; k += NT) {
         ly[k] = T(0);
@@ -666,7 +832,8 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
     }
     // ---- setup: D^{-1/2} (workspace, in SD) and t (registers), staged through the thread's own LDS slots
     if constexpr (SPLIT) {
-        strip_setup<T, NN, R, SD, SE>(e, sd, tb, c, b * R);
+        if constexpr (WIDE) strip_setup_call<T, NN, R, SD, SE>(e, sd, tb, c, b * R);
+        else strip_setup<T, NN, R, SD, SE>(e, sd, tb, c, b * R);
     } else {
         // column i of e, rows j-1, j, j+1 carried along the strip (j = g + 1)
         double eS = e[(b * R) * NP1 + i], eC = e[(b * R + 1) * NP1 + i];
@@ -677,7 +844,7 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
             double sdv = 1.0, tv = 0.0;
             if (c < NN - 1 && g < NN - 1) {
                 const double S = e[j * NP1 + i + 1] + e[j * NP1 + i - 1] + eN + eS;
-                const double rs = 1.0 / sqrt(eC * S);   // h / sqrt(eC S) and sqrt(eC / S) from one root
+                const double rs = rsqrt64(eC * S);   // h / sqrt(eC S) and sqrt(eC / S) from one root
                 sdv = h * rs;
                 tv = eC * rs;
             }
@@ -693,17 +860,18 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
     __syncthreads();
 
     // the transform's strips of S in registers and its eigenvalues in LDS, beyond the exchange array
-    static_assert(!DST || XBYTES <= DS::LAM_AT, "the exchange array keeps off the eigenvalues");
+    float* lamt = nullptr;
     DstStrips<NN, NW> strips;
     if constexpr (DST) {
+        lamt = reinterpret_cast<float*>(smem + onchip_lam_at<T, NN, NW, KEEP>());
         strips.load(Stab, lamtab, wave, lane);
-        dst_stage_lam<NN, NW>(smem, lamtab);
+        dst_stage_lam<NN, NW>(lamt, lamtab);
     }
     // z = L^{-1} r into Z[g][c] (LDS), with the barriers of the four products
     int napp = 0;   // preconditioner applications (same in every thread)
     auto precondition = [&](const T (&rin)[R], double rrin) __attribute__((always_inline)) {
         if constexpr (DST) {
-            dst_apply<T, NN, R, NW>(rin, rrin, smem, strips, c, b, wave, lane);
+            dst_apply<T, NN, R, NW>(rin, rrin, smem, lamt, strips, c, b, wave, lane);
             ++napp;
         }
     };
@@ -723,7 +891,8 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
             const int node = obs[tid];
             const int jj = node / NP1, ii = node % NP1;
             const bool in = ii >= 1 && ii <= NN - 1 && jj >= 1 && jj <= NN - 1;
-            if (in) val = x64[(jj - 1) * NN + ii - 1];
+            if (KEEP && in) val = x64[(jj - 1) * NN + ii - 1];
+            if (!KEEP) val = src_w[tid];   // the node's corrections, summed as they were made
             if (!good) val = NAN;
             if (a.G) a.G[row * a.n_obs + tid] = val;
             src_w[tid] = 2.0 * a.inv2s2 * (val - a.y[tid]);
@@ -736,6 +905,15 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
         }
         __syncthreads();
     };
+    if constexpr (!KEEP) {   // the observed nodes and their running sums (read after the next barrier)
+        if (tid < a.n_obs) {
+            const int node = obs[tid];
+            const int jj = node / NP1, ii = node % NP1;
+            const bool in = ii >= 1 && ii <= NN - 1 && jj >= 1 && jj <= NN - 1;
+            src_at[tid] = in ? (jj - 1) * NN + ii - 1 : -1;
+            src_w[tid] = 0.0;
+        }
+    }
 
     // ---- pass 0: forward problem A w = f into x64 (skipped when x64 already holds w);
     //      pass 1 (ADJ): adjoint problem A lam = P^T (P w - y) / sigma^2 into a.lam
@@ -755,12 +933,18 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
             return s;
         };
         ok = false;
-        double fnorm = 0.0;
+        double fnorm = 0.0, rr64 = 0.0;
         // ---- refinement sweeps
         for (int sweep = 0;; ++sweep) {
             ++sweeps;
             double acc = 0.0;
-            if constexpr (SPLIT) {
+            if constexpr (!KEEP) {   // the residual: f at first, then as the last step left it
+                if (sweep == 0) {
+                    rr64 = a.f * a.f * (double)((NN - 1) * (NN - 1));
+                    if constexpr (WIDE) strip_first_call<T, NN, R, SD>(sd, lout, c, b * R, a.f);
+                    else strip_first<T, NN, R, SD>(sd, lout, c, b * R, a.f);
+                }
+            } else if constexpr (SPLIT) {
                 acc = (pass == 1) ? strip_residual<T, NN, R, true, SD, SE>(e, xo, sd, tb, c, b * R, sweep == 0, a.f, src_w,
                                                                    src_at, a.n_obs)
                                   : strip_residual<T, NN, R, false, SD, SE>(e, xo, sd, tb, c, b * R, sweep == 0, a.f, src_w,
@@ -807,11 +991,11 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
                     xC = xN;
                 }
             }
-            const double rr64 = block_sum<NW>(acc, red2);
+            if constexpr (KEEP) rr64 = block_sum<NW>(acc, red2);
             if (sweep == 0) fnorm = sqrt(rr64);
             if (sqrt(rr64) <= a.tol64 * fnorm) {   // at sweep 0 only for a zero right-hand side
                 ok = true;
-                if (sweep == 0) {
+                if (KEEP && sweep == 0) {
 #pragma unroll 1
                     for (int r = 0; r < R; ++r) xo[(b * R + r) * NN + c] = 0.0;
                 }
@@ -822,7 +1006,7 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
             double tacc = 0.0;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                rv[r] = tb[NN + 1 + r * NN];
+                rv[r] = KEEP ? tb[NN + 1 + r * NN] : lout[(b * R + r) * NN + c];
                 x[r] = T(0);
                 tacc += (double)rv[r] * (double)rv[r];
             }
@@ -908,7 +1092,15 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
             __syncthreads();
 #pragma unroll
             for (int r = 0; r < R; ++r) tb[NN + 1 + r * NN] = x[r];
-            if constexpr (SPLIT) {
+            if constexpr (!KEEP) {
+                if constexpr (WIDE)
+                    acc = strip_refine_call<T, NN, R, SD, SE>(e, xo, sd, ly, lout, c, b * R, sweep == 0, a.f, a.n_obs);
+                else
+                    acc = strip_refine<T, NN, R, SD, SE>(e, xo, sd, ly, lout, c, b * R, sweep == 0, a.f, a.n_obs);
+                rr64 = block_sum<NW>(acc, red2);
+                if (broke) break;
+                continue;
+            } else if constexpr (SPLIT) {
                 strip_update<T, NN, R, SD>(xo, sd, tb, c, b * R, sweep == 0);
             } else {
 #pragma unroll 1
@@ -942,12 +1134,19 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
     __syncthreads();   // the next body may reuse the LDS
 }
 
-template <typename T, int NN, int R, bool DST, bool ADJ, bool AONLY = false>
-__global__ __launch_bounds__(NN * NN / R) void cg_onchip(SolveArgs a, const _Float16* __restrict__ Stab,
+// Waves per SIMD a kernel's registers must leave room for: two workgroups per compute unit at 64^2
+// and below (FP32, observations only).
+template <typename T, int NN, int R, bool KEEP>
+constexpr int onchip_waves() {
+    return (!KEEP && std::is_same<T, float>::value && NN <= 64 && R <= 8) ? cmax(1, 2 * NN * NN / R / 256) : 1;
+}
+
+template <typename T, int NN, int R, bool DST, bool ADJ, bool AONLY = false, bool KEEP = true>
+__global__ __launch_bounds__(NN * NN / R, (onchip_waves<T, NN, R, KEEP>())) void cg_onchip(SolveArgs a, const _Float16* __restrict__ Stab,
                                                          const float* __restrict__ lamtab) {
-    __shared__ __align__(16) unsigned char smem[onchip_smem<T, NN, R, DST>()];
+    __shared__ __align__(16) unsigned char smem[onchip_smem<T, NN, R, DST, KEEP>()];
     __shared__ SolveShared sh;
-    cg_onchip_body<T, NN, R, DST, ADJ, true, AONLY>(a, blockIdx.x, a.obs, smem, sh, Stab, lamtab);
+    cg_onchip_body<T, NN, R, DST, ADJ, true, AONLY, KEEP>(a, blockIdx.x, a.obs, smem, sh, Stab, lamtab);
 }
 
 // Same method (Jacobi-scaled CG, product form) with every vector in global memory, for grids
@@ -966,8 +1165,8 @@ constexpr int D256_BYTES = 256 * D256_LD * 2;
 // LDS named at module level: the mixed-grid solve's bodies and the 256^2 transform below are
 // functions of their own (register-allocated apart from their callers), and LDS they name directly
 // keeps its LDS instructions, where a pointer passed in would turn into generic accesses.
-constexpr int MIXED_SMEM = cmax(cmax(D256_BYTES, onchip_smem<float, 128, 16, true>()),
-                                cmax(onchip_smem<float, 64, 4, true>(), onchip_smem<double, 64, 4, false>()));
+constexpr int MIXED_SMEM = cmax(cmax(D256_BYTES, onchip_smem<float, 128, 16, true, false>()),
+                                cmax(onchip_smem<float, 64, 4, true, false>(), onchip_smem<double, 64, 4, false>()));
 __shared__ __align__(16) unsigned char g_mixed_smem[MIXED_SMEM];
 
 // Four-wide loads and stores of the global solvers' vectors (FP32 or FP64).
@@ -1129,7 +1328,7 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
         if (interior(g, c)) {
             const double eP = e[j * NP1 + i];
             const double S = e[j * NP1 + i + 1] + e[j * NP1 + i - 1] + e[(j + 1) * NP1 + i] + e[(j - 1) * NP1 + i];
-            const double rs = 1.0 / sqrt(eP * S);   // h / sqrt(eP S) and sqrt(eP / S) from one root
+            const double rs = rsqrt64(eP * S);   // h / sqrt(eP S) and sqrt(eP / S) from one root
             sdv = h * rs;
             tt = eP * rs;
         }
@@ -1535,8 +1734,8 @@ __shared__ SolveShared g_mixed_sh;
 template <typename T, int NN, int R, bool DST, bool SE = true>
 __device__ __noinline__ void mixed_onchip(const SolveArgs& a, int64_t p, const int32_t* obs, const void* S,
                                           const float* lam) {
-    static_assert(onchip_smem<T, NN, R, DST>() <= MIXED_SMEM, "mixed-grid LDS");
-    cg_onchip_body<T, NN, R, DST, false, SE>(a, p, obs, g_mixed_smem, g_mixed_sh, reinterpret_cast<const _Float16*>(S),
+    static_assert(onchip_smem<T, NN, R, DST, !DST>() <= MIXED_SMEM, "mixed-grid LDS");
+    cg_onchip_body<T, NN, R, DST, false, SE, false, !DST>(a, p, obs, g_mixed_smem, g_mixed_sh, reinterpret_cast<const _Float16*>(S),
                                          lam);
 }
 
@@ -1734,16 +1933,16 @@ __device__ __forceinline__ int64_t list_item(const unsigned long long* counters,
 }
 
 template <typename T, int NN, int R>
-__global__ __launch_bounds__(NN * NN / R) void solve_list_onchip(SolveArgs a, const int32_t* __restrict__ list,
+__global__ __launch_bounds__(NN * NN / R, (onchip_waves<T, NN, R, false>())) void solve_list_onchip(SolveArgs a, const int32_t* __restrict__ list,
                                                                  const unsigned long long* counters, int lvl,
                                                                  const int32_t* __restrict__ obs,
                                                                  const _Float16* __restrict__ Stab,
                                                                  const float* __restrict__ lamtab) {
-    __shared__ __align__(16) unsigned char smem[onchip_smem<T, NN, R, true>()];
+    __shared__ __align__(16) unsigned char smem[onchip_smem<T, NN, R, true, false>()];
     __shared__ SolveShared sh;
     const int64_t p = list_item(counters, lvl, list);
     if (p < 0) return;
-    cg_onchip_body<T, NN, R, true, false>(a, p, obs, smem, sh, Stab, lamtab);
+    cg_onchip_body<T, NN, R, true, false, true, false, false>(a, p, obs, smem, sh, Stab, lamtab);
 }
 
 template <typename T, int NN>
@@ -1826,6 +2025,8 @@ static hipError_t run_onchip(int64_t N, const SolveArgs& a, const void* S, const
     const _Float16* Sb = reinterpret_cast<const _Float16*>(S);
     if (a.lam)
         cg_onchip<T, NN, R, DST, true><<<dim3((unsigned)N), dim3(NN * NN / R), 0, s>>>(a, Sb, lam);
+    else if (DST && !a.keep)
+        cg_onchip<T, NN, R, DST, false, false, !DST><<<dim3((unsigned)N), dim3(NN * NN / R), 0, s>>>(a, Sb, lam);
     else
         cg_onchip<T, NN, R, DST, false><<<dim3((unsigned)N), dim3(NN * NN / R), 0, s>>>(a, Sb, lam);
     return hipGetLastError();

@@ -1,0 +1,55 @@
+"""The on-chip solve that forms only its observations (GPU): they are sums of per-step corrections,
+read from the nodes' slots, while smc_forward_state keeps the whole solution.
+
+Tolerance: both stop on |f - A w| <= 1e-10 |f| in FP64, and the contract for observations from that
+is 1e-9 relative to the largest; against the oracle's direct solve each is held to it.
+"""
+import json
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import inputs
+from conftest import golden
+from oracle.forward import observe, solve
+from oracle.problem import Problem as OProblem, synthesize
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def corners(n):
+    """Observation nodes at the edges of the grid and of the solver's strips and waves, 64 in all."""
+    at = sorted({1, 2, n // 4, n // 4 + 1, n // 2 - 1, n // 2, n - 2, n - 1})
+    return [[i, j] for i in at for j in at]
+
+
+@pytest.mark.parametrize("f", [1.0, -3.7, 0.0])
+@pytest.mark.parametrize("n,rows,prec", [(32, 4, 1), (32, 8, 1), (32, 0, 0), (64, 4, 1), (64, 8, 1), (64, 16, 1),
+                                         (64, 0, 0), (128, 16, 1), (128, 32, 1)])
+def test_observations_only(n, rows, prec, f):
+    from paper_2503_16028_amd import smc
+    print("[case] refine", n, rows, prec, f, flush=True)
+    sys.stdout.flush()
+    d = json.load(open(golden("problem_t2.json")))
+    d.update(grids=[n], obs_den=n, obs=corners(n), y=[0.0] * 64, f=f, sigma=1.0)
+    op = OProblem(d)
+    N = 3
+    p = smc.Problem(d, N, tol64=1e-10, tol_inner=1e-3)
+    if rows:
+        smc.smc_set_tile(p, 0, rows)
+    x = inputs.particles(N, op.K, 61)
+    xi = torch.tensor(x, device=DEV)
+    G = torch.full((N, 64), np.nan, dtype=torch.float64, device=DEV)
+    K = torch.full_like(G, np.nan)
+    w = torch.empty(N, n * n, dtype=torch.float64, device=DEV)
+    smc.smc_forward_batch(p, N, xi, None, prec, G)
+    smc.smc_forward_state(p, N, xi, prec, K, w)
+    torch.cuda.synchronize()
+    assert smc.smc_status_flags(p) == 0
+    for k in range(N):
+        ref = observe(op, solve(op, synthesize(op, x[k], n), n), n)
+        for got in (G[k].cpu().numpy(), K[k].cpu().numpy()):
+            assert np.abs(got - ref).max() <= 1e-9 * np.abs(ref).max()
