@@ -91,6 +91,43 @@ extern "C" uint64_t smc_philox_u53(uint64_t seed, uint64_t ctr, uint32_t block, 
     return ((uint64_t)(c0 >> 5) << 26) | (uint64_t)(c1 >> 6);
 }
 
+// w0 = L^{-1} 1 on the padded n x n block (zero at index n - 1), up to a factor: the first direction of
+// the forward solves.  Along one axis it is expanded in the sine modes that meet the constant (even
+// index, symmetric about the middle); for mode k the other axis is the three-point problem
+// (lam_k + T) y = 1, T = (-1, 2, -1) / 4, with the solution y_j = (1 - (r^j + r^{n-j}) / (1 + r^n)) / lam_k
+// at node j, where r is the smaller root of r + 1 / r = 2 + 4 lam_k.  Half the nodes of each axis by
+// symmetry.
+static void poisson_state(int n, const std::vector<double>& S, const float* lam, float* w) {
+    const int h = n / 2;   // index h - 1 is the middle node: index g mirrors n - 2 - g
+    std::vector<float> Y((size_t)h * h), row(h);
+    std::vector<double> q(n + 1);
+    for (int k = 0; k < h; ++k) {
+        const double lk = lam[2 * k], cosh1 = 1.0 + 2.0 * lk, r = cosh1 - std::sqrt(cosh1 * cosh1 - 1.0);
+        double ones = 0.0;
+        for (int c = 0; c < n - 1; ++c) ones += S[(size_t)2 * k * n + c];   // S is symmetric
+        q[0] = 1.0;
+        for (int j = 1; j <= n; ++j) q[j] = q[j - 1] * r;
+        for (int c = 0; c < h; ++c)
+            Y[(size_t)k * h + c] = (float)(ones * (1.0 - (q[c + 1] + q[n - c - 1]) / (1.0 + q[n])) / lk);
+    }
+    float top = 0.0f;
+    for (int g = h - 1; g >= 0; --g) {   // the middle row first: it holds the largest value
+        std::fill(row.begin(), row.end(), 0.0f);
+        for (int k = 0; k < h; ++k) {
+            const float sk = (float)S[(size_t)g * n + 2 * k];
+            const float* y = &Y[(size_t)k * h];
+            for (int c = 0; c < h; ++c) row[c] += sk * y[c];
+        }
+        if (g == h - 1) top = row[h - 1];
+        for (int c = 0; c < h; ++c) {
+            const float v = row[c] / top;
+            for (int gg : {g, n - 2 - g})
+                for (int cc : {c, n - 2 - c}) w[(size_t)gg * n + cc] = v;
+        }
+    }
+    for (int k = 0; k < n; ++k) w[(size_t)(n - 1) * n + k] = w[(size_t)k * n + n - 1] = 0.0f;
+}
+
 extern "C" int smc_problem_create(const smc_problem_desc* d, smc_problem* out) {
     if (!d || !out) return fail(SMC_E_INVAL, "desc and out must not be NULL");
     if (d->dim != 1 && d->dim != 2) return fail(SMC_E_INVAL, "dim must be 1 or 2 (got %d)", d->dim);
@@ -208,7 +245,7 @@ extern "C" int smc_problem_create(const smc_problem_desc* d, smc_problem* out) {
             // column (the boundary padding node n) are exactly zero.  FP16: the solvers scale their
             // transform operands into FP16's range
             std::vector<double> S((size_t)n * n);
-            std::vector<float> lam(n);
+            std::vector<float> lam(n + (n >= DST_W0_MIN ? (size_t)n * n : 0));
             for (int r = 0; r < n; ++r) {
                 lam[r] = (float)std::pow(std::sin(M_PI * (r + 1) / (2.0 * n)), 2);
                 for (int q = 0; q < n; ++q)
@@ -216,6 +253,7 @@ extern "C" int smc_problem_create(const smc_problem_desc* d, smc_problem* out) {
                                                ? 0.0
                                                : std::sqrt(2.0 / n) * std::sin(M_PI * (double)((r + 1) * (q + 1)) / n);
             }
+            if (n >= DST_W0_MIN) poisson_state(n, S, lam.data(), lam.data() + n);
             std::vector<_Float16> Sh(S.size());
             for (size_t k = 0; k < S.size(); ++k) Sh[k] = (_Float16)(float)S[k];
             ck(upload((_Float16**)&P.lv[l].dst_S, Sh.data(), Sh.size()));

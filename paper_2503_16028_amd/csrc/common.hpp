@@ -21,12 +21,15 @@ constexpr int KIND_L2MIX = 1;        // no forward map: mixture likelihood in L^
 constexpr int KLP = 32;          // 2D modes per axis, padded, in the synthesis tiles
 constexpr uint32_t UNIFORM_BLOCK = 0x80000000u;
 
+constexpr int DST_W0_MIN = 128;   // grids whose forward solves start from w0
+
 struct Level {
     int n = 0;                   // intervals per axis
     double* basis = nullptr;     // 2D: [(n+1)][KLP] c_k cos(k pi i / n); 1D: [(n+1)][kl] sqrt2 sin(k pi i / n)
     int32_t* obs_node = nullptr; // [n_obs] flat nodal index (2D j*(n+1)+i, 1D i)
     void* dst_S = nullptr;       // [n][n] FP16 sine transform (fast-Poisson preconditioner)
-    float* dst_lam = nullptr;    // [n] its 1D eigenvalues sin^2(pi (k+1) / 2n)
+    float* dst_lam = nullptr;    // [n] its 1D eigenvalues sin^2(pi (k+1) / 2n), then (n >= DST_W0_MIN)
+                                 // [n][n] w0 = L^{-1} 1, the first direction of the forward solves
     int rows = 0;                // tile of the fast-Poisson solver: grid rows per thread (0 = default)
 };
 

@@ -1011,16 +1011,33 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
                 tacc += (double)rv[r] * (double)rv[r];
             }
             double rr, rz;
+            // The forward problem's first direction is w0 = L^{-1} 1 from a table instead of the
+            // preconditioned residual: the right-hand side D^{-1/2} f is smooth, so the first residual the
+            // preconditioner can do something about is the second.  A solve then needs one transform less
+            // (9.0 -> 8.1 at 128^2, the same iterations): 4096 potentials 1.92 -> 1.85 ms.  Only with
+            // refinement: one long FP64 sweep loses the third direction's conjugacy to the first (a stage
+            // of 1024 at 64^2 3.34 -> 3.41 ms).  Not up to 64^2, where two workgroups share a compute
+            // unit's registers and the branch costs more than the transform (4096 potentials 423 -> 436
+            // us), nor where the solution is kept (the same).
+            bool w_first = false;
+            if constexpr (DST && !KEEP && NN >= DST_W0_MIN && std::is_same<T, float>::value) w_first = sweep == 0;
             if constexpr (DST) {
+                if (w_first) {
+                    const gcbp w0 = uniform_base(lamtab);
+                    const uint32_t at = (uint32_t)(NN + b * R * NN + c) * 4u;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) p[r] = (T)at_off<float>(w0, at + r * NN * 4u);
+                }
                 rr = block_sum<NW>(tacc, red1);   // also the transform's input scale
-                __syncthreads();                  // the transform buffers alias the staging slots
-                precondition(rv, rr);
+                if (!w_first) {
+                    __syncthreads();              // the transform buffers alias the staging slots
+                    precondition(rv, rr);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) p[r] = zval(r);
+                }
                 double zacc = 0.0;
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    p[r] = zval(r);
-                    zacc += (double)rv[r] * (double)p[r];
-                }
+                for (int r = 0; r < R; ++r) zacc += (double)rv[r] * (double)p[r];
                 rz = block_sum<NW>(zacc, red2);
             } else {
 #pragma unroll
@@ -1058,15 +1075,30 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
                 if (!(pq > 0.0) || !(pq < INFINITY)) { broke = true; break; }
                 const T alpha = (T)(rz / pq);
                 T r_acc = T(0);
+                if (w_first) {   // x = alpha p waits: until the next direction is made conjugate, x holds q
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    x[r] += alpha * p[r];
-                    rv[r] -= alpha * q[r];
-                    r_acc += rv[r] * rv[r];
+                    for (int r = 0; r < R; ++r) {
+                        x[r] = q[r];
+                        rv[r] -= alpha * q[r];
+                        r_acc += rv[r] * rv[r];
+                    }
+                } else {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        x[r] += alpha * p[r];
+                        rv[r] -= alpha * q[r];
+                        r_acc += rv[r] * rv[r];
+                    }
                 }
                 rr = block_sum<NW>((double)r_acc, red2);
                 ++total;
-                if (!(rr > target)) break;
+                if (!(rr > target)) {
+                    if (w_first) {
+#pragma unroll
+                        for (int r = 0; r < R; ++r) x[r] = alpha * p[r];
+                    }
+                    break;
+                }
                 if constexpr (DST) {
                     precondition(rv, rr);
                     T z[R];
@@ -1077,7 +1109,17 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
                         rz_acc += rv[r] * z[r];
                     }
                     const double rzn = block_sum<NW>((double)rz_acc, red1);
-                    const T beta = (T)(rzn / rz);
+                    T beta = (T)(rzn / rz);
+                    if (w_first) {   // p was no preconditioned residual: conjugate to it by the definition
+                        T zq_acc = T(0);
+#pragma unroll
+                        for (int r = 0; r < R; ++r) {
+                            zq_acc += z[r] * x[r];
+                            x[r] = alpha * p[r];
+                        }
+                        beta = (T)(-block_sum<NW>((double)zq_acc, red2) / pq);
+                        w_first = false;
+                    }
                     rz = rzn;
 #pragma unroll
                     for (int r = 0; r < R; ++r) p[r] = z[r] + beta * p[r];
@@ -1359,6 +1401,8 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
         __syncthreads();
     };
 
+    const bool from_w0 = DST && !ADJ && std::is_same<T, float>::value && !a.keep;   // 256^2: 10.80 -> 10.70 ms per 1024
+
     // pass 0: forward problem into x64 (skipped when given); pass 1 (ADJ): adjoint problem into a.lam
     const int first = (ADJ && a.fwd_given) ? 1 : 0, last = ADJ ? 1 : 0;
     int total = 0, sweeps = 0, solves = 0;
@@ -1380,7 +1424,7 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
             // residual pass: r = D^{-1/2} (f - A x) in T, with |f - A x|^2 in FP64 and |r|^2 summed on
             // the way (the fast-Poisson path writes r only: its first transform writes p = z, and the
             // first update sets x = alpha p)
-            double acc = 0.0, tacc = 0.0;
+            double acc = 0.0, tacc = 0.0, wacc = 0.0;
             for (int k = tid; k < nodes; k += 1024) {
                 const int g = k / NN, c = k % NN, i = c + 1, j = g + 1;
                 T rk = T(0);
@@ -1404,6 +1448,10 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
                 if constexpr (!DST) {
                     pv[k] = rk;
                     xv[k] = T(0);
+                } else if (from_w0 && sweep == 0) {
+                    const T w0 = (T)lamtab[NN + k];
+                    pv[k] = w0;
+                    wacc += (double)rk * (double)w0;
                 }
             }
             const double rr64 = block_sum<NW>(acc, red2);
@@ -1427,9 +1475,17 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
                 // p = z = L^{-1} r straight from the transform, with r.z summed as z is stored
                 T* pc = pv;    // current search direction
                 T* pn = pv2;   // the next one, written while pc is read (neighbours read pc)
-                double rz = block_sum<NW>(dstg_precondition<DN, T>(rv, pc, Stab, lamtab, 0, norm_exponent(rr) + 3, 1),
-                                          red2);
-                ++napp;
+                // the forward problem's first direction is w0 = L^{-1} 1 (see cg_onchip_body), written to p
+                // with the residual; then r.p was summed there too
+                bool w_first = from_w0 && sweep == 0;
+                double rz;
+                if (w_first) {
+                    rz = block_sum<NW>(wacc, red2);
+                } else {
+                    rz = block_sum<NW>(dstg_precondition<DN, T>(rv, pc, Stab, lamtab, 0, norm_exponent(rr) + 3, 1),
+                                       red2);
+                    ++napp;
+                }
                 // Per iteration three passes over the global vectors: the stencil, which first forms
                 // p <- z + beta p (on the fly at the neighbours too; p is double-buffered because
                 // neighbouring rows read the old one), the x/r update (which also stages fp16(r 2^-ex)
@@ -1529,6 +1585,15 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
                         ++napp;
                     }
                     beta = (T)(rzn / rz);
+                    if (w_first) {   // conjugate to w0 by the definition (it was no preconditioned residual)
+                        double zq = 0.0;
+                        for (int k = 4 * tid; k < nodes; k += 4096) {
+                            const T4 z4 = ld4(zv + k), q4 = ld4(qv + k);
+                            zq += (double)(z4.x * q4.x + z4.y * q4.y) + (double)(z4.z * q4.z + z4.w * q4.w);
+                        }
+                        beta = (T)(-block_sum<NW>(zq, red2) / pq);
+                        w_first = false;
+                    }
                     rz = rzn;
                 }
                 if (first_it) have_x = false;   // no update ran: the correction is zero
