@@ -494,6 +494,8 @@ static SolveArgs solve_args(const Problem& P, int level) {
     a.x_stride = P.x_stride;
     a.sd_stride = P.x_stride;
     a.vec_stride = P.vec_stride;
+    a.aux = P.ws_lam;   // free while no adjoint is solved
+    a.aux_stride = P.x_stride;
     a.lam = nullptr;
     a.lam_stride = P.x_stride;
     a.fwd_given = 0;
@@ -566,7 +568,7 @@ static hipError_t forward_levels(smc_problem_s* ps, int prec, int64_t N, const d
         for (int l = 0; l < P.n_levels; ++l) rows[l] = P.lv[l].rows;
         e = launch_solve_levels(prec, N, a, lt, rows, P.ws_list, P.ws_counters, P.n_cu, s);
     } else {
-        e = launch_solve_mixed(prec, dst, N, a, lt, o.level, P.ws_list, P.ws_counters, P.n_cu, s);
+        e = launch_solve_mixed(prec, N, a, lt, o.level, P.ws_list, P.ws_counters, P.n_cu, s);
     }
     if (e != hipSuccess) return e;
     if (rec) e = record(ps->pool, s);

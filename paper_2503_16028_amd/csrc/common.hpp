@@ -198,6 +198,8 @@ struct SolveArgs {
     double* sd;          // D^{-1/2}, row stride x_stride (doubles; an FP32 row starts at the same place)
     void* vec;           // global-solver vectors, row stride vec_stride (doubles)
     int64_t e_stride, x_stride, sd_stride, vec_stride;
+    double* aux;         // scratch of a forward solve that does not keep its solution, row stride aux_stride
+    int64_t aux_stride;  // (at least n^2 doubles a row)
     double* lam;         // adjoint solution [N][lam_stride] (interior layout as x64), or null: no adjoint
     int64_t lam_stride;
     int keep;            // the whole FP64 solution is wanted in x64 (on-chip solvers may else form only
@@ -303,9 +305,9 @@ hipError_t launch_plan(int64_t N, const int32_t* level, const LevelTable& lt, in
 // refinement or FP64, fast-Poisson preconditioners on every grid.
 hipError_t launch_solve_levels(int prec, int64_t N, const SolveArgs& a, const LevelTable& lt, const int* rows,
                                const int32_t* list, unsigned long long* counters, int n_cu, hipStream_t s);
-hipError_t launch_solve_mixed(int prec, bool dst, int64_t N, const SolveArgs& a, const LevelTable& lt,
-                              const int32_t* level, const int32_t* list, unsigned long long* counters, int grid,
-                              hipStream_t s);
+// The solves of a level map without the fast-Poisson preconditioner, in one persistent launch.
+hipError_t launch_solve_mixed(int prec, int64_t N, const SolveArgs& a, const LevelTable& lt, const int32_t* level,
+                              const int32_t* list, unsigned long long* counters, int grid, hipStream_t s);
 hipError_t launch_synth2d(const double* xi, int K, int kl, const double* sqrt_lam, const double* basis, int n,
                           double* out, int64_t out_stride, int64_t N, bool exp_half, hipStream_t s);
 hipError_t launch_synth1d(const double* xi, int kl, const double* sqrt_lam, const double* basis, int n, double* out,

@@ -1401,8 +1401,6 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
         __syncthreads();
     };
 
-    const bool from_w0 = DST && !ADJ && std::is_same<T, float>::value && !a.keep;   // 256^2: 10.80 -> 10.70 ms per 1024
-
     // pass 0: forward problem into x64 (skipped when given); pass 1 (ADJ): adjoint problem into a.lam
     const int first = (ADJ && a.fwd_given) ? 1 : 0, last = ADJ ? 1 : 0;
     int total = 0, sweeps = 0, solves = 0;
@@ -1424,7 +1422,7 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
             // residual pass: r = D^{-1/2} (f - A x) in T, with |f - A x|^2 in FP64 and |r|^2 summed on
             // the way (the fast-Poisson path writes r only: its first transform writes p = z, and the
             // first update sets x = alpha p)
-            double acc = 0.0, tacc = 0.0, wacc = 0.0;
+            double acc = 0.0, tacc = 0.0;
             for (int k = tid; k < nodes; k += 1024) {
                 const int g = k / NN, c = k % NN, i = c + 1, j = g + 1;
                 T rk = T(0);
@@ -1448,10 +1446,6 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
                 if constexpr (!DST) {
                     pv[k] = rk;
                     xv[k] = T(0);
-                } else if (from_w0 && sweep == 0) {
-                    const T w0 = (T)lamtab[NN + k];
-                    pv[k] = w0;
-                    wacc += (double)rk * (double)w0;
                 }
             }
             const double rr64 = block_sum<NW>(acc, red2);
@@ -1475,17 +1469,9 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
                 // p = z = L^{-1} r straight from the transform, with r.z summed as z is stored
                 T* pc = pv;    // current search direction
                 T* pn = pv2;   // the next one, written while pc is read (neighbours read pc)
-                // the forward problem's first direction is w0 = L^{-1} 1 (see cg_onchip_body), written to p
-                // with the residual; then r.p was summed there too
-                bool w_first = from_w0 && sweep == 0;
-                double rz;
-                if (w_first) {
-                    rz = block_sum<NW>(wacc, red2);
-                } else {
-                    rz = block_sum<NW>(dstg_precondition<DN, T>(rv, pc, Stab, lamtab, 0, norm_exponent(rr) + 3, 1),
-                                       red2);
-                    ++napp;
-                }
+                double rz = block_sum<NW>(dstg_precondition<DN, T>(rv, pc, Stab, lamtab, 0, norm_exponent(rr) + 3, 1),
+                                          red2);
+                ++napp;
                 // Per iteration three passes over the global vectors: the stencil, which first forms
                 // p <- z + beta p (on the fly at the neighbours too; p is double-buffered because
                 // neighbouring rows read the old one), the x/r update (which also stages fp16(r 2^-ex)
@@ -1585,15 +1571,6 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
                         ++napp;
                     }
                     beta = (T)(rzn / rz);
-                    if (w_first) {   // conjugate to w0 by the definition (it was no preconditioned residual)
-                        double zq = 0.0;
-                        for (int k = 4 * tid; k < nodes; k += 4096) {
-                            const T4 z4 = ld4(zv + k), q4 = ld4(qv + k);
-                            zq += (double)(z4.x * q4.x + z4.y * q4.y) + (double)(z4.z * q4.z + z4.w * q4.w);
-                        }
-                        beta = (T)(-block_sum<NW>(zq, red2) / pq);
-                        w_first = false;
-                    }
                     rz = rzn;
                 }
                 if (first_it) have_x = false;   // no update ran: the correction is zero
@@ -1660,6 +1637,394 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
     __syncthreads();
 }
 
+// ------------------------------------------------------------------ global-memory solver, observations only
+// The fast-Poisson conjugate gradients of the 128^2 (FP64) and 256^2 grids when only the observations
+// are wanted (not the whole solution).  The method and the operator are cg_global_body's; what it moves
+// is less, and at 256^2 the solve is bound by that (the vectors of one particle per compute unit are
+// 460 MB, past the last-level cache: 1024 solves moved 40 MB each at 4.3 TB/s, where a large copy
+// reaches 4.7).  An iteration
+//   - keeps its search direction in a buffer of its own instead of adding it to x: the correction is
+//     sum alpha_k p_k once at the end of the sweep (directions are folded into x when the buffers are
+//     used up), so x and p are not read and x is not written per iteration: 10 vector passes, were 13;
+//   - takes the horizontal neighbours from the adjacent lanes.
+// A refinement step rounds dx = D^{-1/2} y to T and updates the FP64 residual, as strip_refine does; the
+// FP64 passes run down columns, the vertical neighbours carried in registers.  The passes over the
+// vectors keep a few loads in flight per thread and leave the rest to the sixteen waves: unrolled
+// further they spill, and scratch traffic is what this solver can least afford.  Measured: 1024 solves
+// at 256^2 in FP32 10.70 -> 7.73 ms, 32 solves 1.45 -> 0.93 ms, 1001 at 128^2 in FP64 2.77 -> 2.63 ms.
+// Vector slots of a particle's row of a.vec (7 n^2 doubles): t, r, q, z, then the directions; FP32 has
+// the last one for x, FP64 keeps x in a.aux.
+template <typename T, int NN>
+struct GlobalSlots {
+    static constexpr bool F32 = std::is_same<T, float>::value;
+    static constexpr int NP = F32 ? 9 : 3;   // direction buffers
+};
+
+// four consecutive values of a row that starts on any element
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double d4u __attribute__((ext_vector_type(4), aligned(8)));
+template <typename S> struct Vec4U;
+template <> struct Vec4U<float> { using type = f4u; };
+template <> struct Vec4U<double> { using type = d4u; };
+
+// Column c, rows g0 .. g0 + R - 1: D^{-1/2}, t and the first scaled residual D^{-1/2} f into memory;
+// adds |r|^2 to rr and (W0) r.w0 to rw.
+template <typename T, int NN, int R, typename SD, bool W0>
+__device__ __noinline__ double2 gstrip_setup(const double* __restrict__ e_, SD* __restrict__ sd_, T* __restrict__ t_,
+                                             T* __restrict__ r_, const float* __restrict__ w0_, int c, int g0,
+                                             double f) {
+    constexpr int NP1 = NN + 1;
+    const double h = 1.0 / NN;
+    const gcbp e = uniform_base(e_), sd = uniform_base(sd_), t = uniform_base(t_), rb = uniform_base(r_),
+               w0 = uniform_base(w0_);
+    const int i = c + 1, lane = threadIdx.x & 63;
+    const int c0 = __builtin_amdgcn_readfirstlane(c - lane);
+    const int ieE = min(c0 + 65, NN), ieW = c0;
+    kcdp eu = (kcdp)wave_uniform(e_);
+    const int g0u = __builtin_amdgcn_readfirstlane(g0);
+    const uint32_t own = (uint32_t)(g0 * NN + c), eown = (uint32_t)((g0 + 1) * NP1 + i) * 8u;
+    double eS = at_off<double>(e, eown - NP1 * 8u), eC = at_off<double>(e, eown);
+    double rr = 0.0, rw = 0.0;
+    constexpr int B = 4;   // sixteen waves hide the latency; eight rows spill
+    static_assert(R % B == 0 && NN % 64 == 0, "strip blocking");
+#pragma unroll 1
+    for (int r0 = 0; r0 < R; r0 += B) {
+        const uint32_t at = own + (uint32_t)(r0 * NN), eat = eown + (uint32_t)(r0 * NP1) * 8u;
+        double eN[B], eEe[B], eWe[B];
+        float wv[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const uint32_t up = k + 1 < B || g0 + r0 + B < NN ? NP1 * 8u : 0u;   // never past row n
+            const int ju = g0u + r0 + k + 1;
+            eN[k] = at_off<double>(e, eat + k * NP1 * 8u + up);
+            eEe[k] = eu[ju * NP1 + ieE];
+            eWe[k] = eu[ju * NP1 + ieW];
+            wv[k] = W0 ? at_off<float>(w0, (at + k * NN) * 4u) : 0.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const bool in = c < NN - 1 && g0 + r0 + k < NN - 1;
+            const double S = from_next_lane(eC, eEe[k]) + from_prev_lane(eC, eWe[k]) + eN[k] + eS;
+            const double rs = rsqrt64(eC * S);   // h / sqrt(eC S) and sqrt(eC / S) from one root
+            const SD sv = in ? (SD)(h * rs) : SD(1);
+            const T rv = in ? (T)((double)sv * f) : T(0);
+            put_off<SD>(sd, (at + k * NN) * (uint32_t)sizeof(SD), sv);
+            put_off<T>(t, (at + k * NN) * (uint32_t)sizeof(T), in ? (T)(eC * rs) : T(0));
+            put_off<T>(rb, (at + k * NN) * (uint32_t)sizeof(T), rv);
+            rr += (double)rv * (double)rv;
+            if (W0) rw += (double)rv * (double)wv[k];
+            eS = eC;
+            eC = eN[k];
+        }
+    }
+    return make_double2(rr, rw);
+}
+
+// The same columns: r64 <- r64 - A dx (r64 = f before the first step) and r = D^{-1/2} r64, with dx in
+// memory (zero on the padding); returns the thread's shares of |r64|^2 and |r|^2.
+template <typename T, int NN, int R, typename SD>
+__device__ __noinline__ double2 gstrip_refine(const double* __restrict__ e_, double* __restrict__ r64_,
+                                              const SD* __restrict__ sd_, const T* __restrict__ dx_,
+                                              T* __restrict__ r_, int c, int g0, bool first, double f) {
+    constexpr int NP1 = NN + 1;
+    const double n2 = (double)NN * (double)NN;
+    const gcbp e = uniform_base(e_), sd = uniform_base(sd_), dx = uniform_base(dx_), rb = uniform_base(r_),
+               r64 = uniform_base(r64_);
+    const int i = c + 1, lane = threadIdx.x & 63;
+    const int c0 = __builtin_amdgcn_readfirstlane(c - lane);
+    const int ieE = min(c0 + 65, NN), ieW = c0;
+    // dx columns beyond the wave's edges (column n - 1 holds zero: so does the one west of column 0)
+    const int cxE = min(c0 + 64, NN - 1), cxW = c0 > 0 ? c0 - 1 : NN - 1;
+    kcdp eu = (kcdp)wave_uniform(e_);
+    const int g0u = __builtin_amdgcn_readfirstlane(g0);
+    const uint32_t own = (uint32_t)(g0 * NN + c), eown = (uint32_t)((g0 + 1) * NP1 + i) * 8u;
+    constexpr uint32_t TS = (uint32_t)sizeof(T);
+    double eS = at_off<double>(e, eown - NP1 * 8u), eC = at_off<double>(e, eown);
+    double dC = (double)at_off<T>(dx, own * TS), dS = g0 > 0 ? (double)at_off<T>(dx, (own - NN) * TS) : 0.0;
+    double acc = 0.0, rr = 0.0;
+    constexpr int B = 4;   // sixteen waves hide the latency; eight rows spill
+    static_assert(R % B == 0 && NN % 64 == 0, "strip blocking");
+#pragma unroll 1
+    for (int r0 = 0; r0 < R; r0 += B) {
+        const uint32_t at = own + (uint32_t)(r0 * NN), eat = eown + (uint32_t)(r0 * NP1) * 8u;
+        double eN[B], ro[B], eEe[B], eWe[B];
+        T dN[B], dEe[B], dWe[B];
+        SD sv[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            // row g + 1; only a strip's last row can be row n (of dx: row n - 1, which holds zero)
+            const bool top = k + 1 == B && g0 + r0 + B == NN;
+            const int gu = g0u + r0 + k;
+            eN[k] = at_off<double>(e, eat + k * NP1 * 8u + (top ? 0u : NP1 * 8u));
+            dN[k] = at_off<T>(dx, (at + k * NN + (top ? 0 : NN)) * TS);
+            sv[k] = at_off<SD>(sd, (at + k * NN) * (uint32_t)sizeof(SD));
+            eEe[k] = eu[(gu + 1) * NP1 + ieE];
+            eWe[k] = eu[(gu + 1) * NP1 + ieW];
+            dEe[k] = at_off<T>(dx, (uint32_t)(gu * NN + cxE) * TS);
+            dWe[k] = at_off<T>(dx, (uint32_t)(gu * NN + cxW) * TS);
+            ro[k] = f;
+        }
+        if (!first) {
+#pragma unroll
+            for (int k = 0; k < B; ++k) ro[k] = at_off<double>(r64, (at + k * NN) * 8u);
+        }
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const double eE = from_next_lane(eC, eEe[k]), eW = from_prev_lane(eC, eWe[k]);
+            const double dE = from_next_lane(dC, (double)dEe[k]), dW = from_prev_lane(dC, (double)dWe[k]);
+            const double dn = (double)dN[k];
+            const double flux = eE * (dC - dE) + eW * (dC - dW) + eN[k] * (dC - dn) + eS * (dC - dS);
+            const bool in = c < NN - 1 && g0 + r0 + k < NN - 1;
+            const double res = in ? ro[k] - eC * n2 * flux : 0.0;
+            const T rv = (T)((double)sv[k] * res);
+            put_off<double>(r64, (at + k * NN) * 8u, res);
+            put_off<T>(rb, (at + k * NN) * TS, rv);
+            acc += res * res;
+            rr += (double)rv * (double)rv;
+            eS = eC;
+            eC = eN[k];
+            dS = dC;
+            dC = dn;
+        }
+    }
+    return make_double2(acc, rr);
+}
+
+// A value of the previous (next) lane, 0 at the wave's ends.
+__device__ __forceinline__ float lane_before(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float lane_after(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xF, 0xF, false));
+}
+__device__ __forceinline__ double lane_before(double v) { return from_prev_lane(v, 0.0); }
+__device__ __forceinline__ double lane_after(double v) { return from_next_lane(v, 0.0); }
+
+template <typename T, int NN>
+__device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int64_t row, const int32_t* __restrict__ obs,
+                                                   SolveShared& sh, _Float16* X, const _Float16* __restrict__ Stab,
+                                                   const float* __restrict__ lamtab) {
+    constexpr int NW = 16, nodes = NN * NN, NP1 = NN + 1, R = nodes / 1024;
+    constexpr bool F32 = GlobalSlots<T, NN>::F32, W0 = F32 && NN >= DST_W0_MIN;
+    constexpr int NP = GlobalSlots<T, NN>::NP;
+    using T4 = vec4_t<T>;
+    using SD = typename std::conditional<F32, float, double>::type;   // as cg_global_body keeps D^{-1/2}
+    const int tid = threadIdx.x, c = tid % NN, b = tid / NN;
+    const double* e = a.e + row * a.e_stride;
+    double* r64 = a.x64 + row * a.x_stride;
+    SD* sd = reinterpret_cast<SD*>(a.sd + row * a.sd_stride);
+    T* vb = reinterpret_cast<T*>(reinterpret_cast<double*>(a.vec) + row * a.vec_stride);
+    T* tv = vb;
+    T* rv = vb + nodes;
+    T* qv = vb + 2 * nodes;
+    T* zv = vb + 3 * nodes;
+    T* pb = vb + 4 * nodes;   // NP directions
+    T* xv = F32 ? vb + 13 * nodes : reinterpret_cast<T*>(a.aux + row * a.aux_stride);
+    const float* w0 = lamtab + NN;
+    double* red1 = sh.red1;
+    double* red2 = sh.red2;
+    __shared__ T alphas[NP];
+    auto interior = [](int g, int cc) { return cc < NN - 1 && g < NN - 1; };
+
+    if (tid < a.n_obs) {   // the observed nodes and the running sums of their corrections
+        const int node = obs[tid];
+        const int jj = node / NP1, ii = node % NP1;
+        sh.src_at[tid] = (ii >= 1 && ii <= NN - 1 && jj >= 1 && jj <= NN - 1) ? (jj - 1) * NN + ii - 1 : -1;
+        sh.src_w[tid] = 0.0;
+    }
+    const double2 s0 = gstrip_setup<T, NN, R, SD, W0>(e, sd, tv, rv, w0, c, b * R, a.f);
+    double rr = block_sum<NW>(s0.x, red1);   // its barrier publishes t and r
+    const double rw = W0 ? block_sum<NW>(s0.y, red2) : 0.0;
+    double rr64 = a.f * a.f * (double)((NN - 1) * (NN - 1));
+    const double fnorm = sqrt(rr64);
+    int total = 0, sweeps = 0, napp = 0;
+    bool ok = false;
+    for (int sweep = 0;; ++sweep) {
+        ++sweeps;
+        if (sqrt(rr64) <= a.tol64 * fnorm) {   // at sweep 0 only for a zero right-hand side
+            ok = true;
+            break;
+        }
+        if (!(rr64 < INFINITY) || sweep >= a.max_sweeps || total >= a.max_iter) break;
+        // the inner solve reduces its residual by tol_inner, or only as far as the outer tolerance
+        // still needs (a margin of 10 for the Jacobi-scaled norm), whichever is less work
+        const double red = fmin(0.5, fmax(a.tol_inner, 0.1 * a.tol64 * fnorm / sqrt(rr64)));
+        const double target = red * red * rr;
+        bool broke = false, have_x = false;
+        int np = 0;   // directions not yet in x
+        bool w_first = W0 && sweep == 0;
+        double rz;
+        if (w_first) {
+            rz = rw;
+        } else {
+            rz = block_sum<NW>(dstg_precondition<NN, T>(rv, pb, Stab, lamtab, 0, norm_exponent(rr) + 3, 1), red2);
+            ++napp;
+        }
+        const T* pc = pb;   // the current direction (FP32: w0's table at first)
+        if constexpr (W0) pc = w_first ? reinterpret_cast<const T*>(w0) : pb;
+        // x <- x + sum of the np directions, taken into x
+        auto direction = [&](int k) -> const T* {
+            if constexpr (W0) return (sweep == 0 && !have_x && k == 0) ? reinterpret_cast<const T*>(w0) : pb + k * nodes;
+            return pb + k * nodes;
+        };
+        auto correction = [&](int k4) -> T4 {
+            T4 y;
+            if (have_x) {
+                const typename Vec4U<T>::type x4 = *reinterpret_cast<const typename Vec4U<T>::type*>(xv + k4);
+                y.x = x4[0]; y.y = x4[1]; y.z = x4[2]; y.w = x4[3];
+            } else {
+                y.x = y.y = y.z = y.w = T(0);
+            }
+#pragma unroll 1
+            for (int k = 0; k < np; ++k) y = fma4(alphas[k], ld4(direction(k) + k4), y);
+            return y;
+        };
+        bool first_it = true;   // p = z as stored
+        T beta = T(0);
+        while (rr > target) {
+            if (total >= a.max_iter) break;
+            const int ex = norm_exponent(rr) + 3;
+            const T sc = (T)ldexpf(1.0f, -ex);
+            T* pn = pb + (first_it ? 0 : np) * nodes;   // where p = z + beta p goes
+            T pq_acc = T(0);
+#pragma unroll 1
+            for (int k = 4 * tid; k < nodes; k += 4096) {   // four consecutive nodes of a row
+                const int g = k / NN, cc = k % NN;
+                const int kN = (g < NN - 1) ? k + NN : k, kS = (g > 0) ? k - NN : k;
+                T4 p4 = ld4(pc + k), pN = ld4(pc + kN), pS = ld4(pc + kS);
+                const T4 t4 = ld4(tv + k), tN = ld4(tv + kN), tS = ld4(tv + kS);
+                if (!first_it) {
+                    const T4 z4 = ld4(zv + k), zN = ld4(zv + kN), zS = ld4(zv + kS);
+                    p4 = fma4(beta, p4, z4);
+                    pN = fma4(beta, pN, zN);
+                    pS = fma4(beta, pS, zS);
+                }
+                const T t_[4] = {t4.x, t4.y, t4.z, t4.w};
+                const T pn_[4] = {pN.x, pN.y, pN.z, pN.w}, tn[4] = {tN.x, tN.y, tN.z, tN.w};
+                const T ps[4] = {pS.x, pS.y, pS.z, pS.w}, ts[4] = {tS.x, tS.y, tS.z, tS.w};
+                T p_[4] = {p4.x, p4.y, p4.z, p4.w};
+                T yc[4], q_[4];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    if (!interior(g, cc + m)) p_[m] = T(0);
+                    yc[m] = t_[m] * p_[m];
+                }
+                // the nodes beyond the four, from the adjacent lanes: at a row's start the lane before
+                // ends in the padding column, which holds zero
+                const T yW0 = lane_before(yc[3]), yE3 = lane_after(yc[0]);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const T yE = (m < 3) ? yc[m < 3 ? m + 1 : 3] : yE3;
+                    const T yW = (m > 0) ? yc[m > 0 ? m - 1 : 0] : yW0;
+                    const T yN = tn[m] * pn_[m];
+                    const T yS = (g > 0) ? ts[m] * ps[m] : T(0);
+                    q_[m] = interior(g, cc + m) ? p_[m] - t_[m] * ((yE + yW) + (yN + yS)) : T(0);
+                    pq_acc += p_[m] * q_[m];
+                }
+                if (!first_it) st4(pn + k, p_[0], p_[1], p_[2], p_[3]);
+                st4(qv + k, q_[0], q_[1], q_[2], q_[3]);
+            }
+            const double pq = block_sum<NW>((double)pq_acc, red1);   // its barriers publish p and q
+            if (!first_it) pc = pn;
+            if (!(pq > 0.0) || !(pq < INFINITY)) {
+                broke = true;
+                break;
+            }
+            const T alpha = (T)(rz / pq);
+            if (tid == 0) alphas[np] = alpha;
+            T r_acc = T(0);
+#pragma unroll 4
+            for (int k = 4 * tid; k < nodes; k += 4096) {
+                T4 r4 = ld4(rv + k);
+                const T4 q4 = ld4(qv + k);
+                r4.x -= alpha * q4.x; r4.y -= alpha * q4.y; r4.z -= alpha * q4.z; r4.w -= alpha * q4.w;
+                r_acc += ((r4.x * r4.x + r4.y * r4.y) + (r4.z * r4.z + r4.w * r4.w));
+                st4(rv + k, r4.x, r4.y, r4.z, r4.w);
+                hf4 hb;
+                hb[0] = (_Float16)(float)(r4.x * sc); hb[1] = (_Float16)(float)(r4.y * sc);
+                hb[2] = (_Float16)(float)(r4.z * sc); hb[3] = (_Float16)(float)(r4.w * sc);
+                *reinterpret_cast<hf4*>(X + (k / NN) * (NN + 8) + (k % NN)) = hb;
+            }
+            rr = block_sum<NW>((double)r_acc, red2);   // its barrier also publishes X and alphas
+            ++total;
+            ++np;
+            first_it = false;
+            if (!(rr > target)) break;
+            double zacc = dstg_precondition<NN, T>(rv, zv, Stab, lamtab, 1, ex, 1);
+            ++napp;
+            double rzn = block_sum<NW>(zacc, red1);
+            if (!(fabs(rzn) < INFINITY)) {   // the residual outgrew the staged scale: redo from r
+                __syncthreads();
+                zacc = dstg_precondition<NN, T>(rv, zv, Stab, lamtab, 0, norm_exponent(rr) + 3, 1);
+                rzn = block_sum<NW>(zacc, red2);
+                ++napp;
+            }
+            beta = (T)(rzn / rz);
+            if (w_first) {   // conjugate to w0 by the definition (it was no preconditioned residual)
+                double zq = 0.0;
+#pragma unroll 2
+                for (int k = 4 * tid; k < nodes; k += 4096) {
+                    const T4 z4 = ld4(zv + k), q4 = ld4(qv + k);
+                    zq += (double)(z4.x * q4.x + z4.y * q4.y) + (double)(z4.z * q4.z + z4.w * q4.w);
+                }
+                beta = (T)(-block_sum<NW>(zq, red2) / pq);
+                w_first = false;
+            }
+            rz = rzn;
+            if (np == NP) {   // no buffer left: fold the directions into x (the last one stays readable)
+#pragma unroll 1
+                for (int k = 4 * tid; k < nodes; k += 4096) {
+                    const T4 y = correction(k);
+                    typename Vec4U<T>::type x4;
+                    x4[0] = y.x; x4[1] = y.y; x4[2] = y.z; x4[3] = y.w;
+                    *reinterpret_cast<typename Vec4U<T>::type*>(xv + k) = x4;
+                }
+                have_x = true;
+                np = 0;
+                __syncthreads();   // every thread has read the alphas and the first buffer
+            }
+        }
+        // refinement: dx = D^{-1/2} y in T (over q), its observed nodes, then the FP64 residual
+        __syncthreads();
+#pragma unroll 1
+        for (int k = 4 * tid; k < nodes; k += 4096) {
+            const T4 y = correction(k);
+            typename Vec4U<SD>::type s4 = *reinterpret_cast<const typename Vec4U<SD>::type*>(sd + k);
+            const int g = k / NN, cc = k % NN;
+            const T d0 = (T)s4[0] * y.x, d1 = (T)s4[1] * y.y, d2 = (T)s4[2] * y.z, d3 = (T)s4[3] * y.w;
+            st4(qv + k, interior(g, cc) ? d0 : T(0), interior(g, cc + 1) ? d1 : T(0), interior(g, cc + 2) ? d2 : T(0),
+                interior(g, cc + 3) ? d3 : T(0));
+        }
+        __syncthreads();
+        if (tid < a.n_obs && sh.src_at[tid] >= 0) sh.src_w[tid] += (double)qv[sh.src_at[tid]];
+        const double2 s1 = gstrip_refine<T, NN, R, SD>(e, r64, sd, qv, rv, c, b * R, sweep == 0, a.f);
+        rr64 = block_sum<NW>(s1.x, red1);   // its barrier publishes r
+        rr = block_sum<NW>(s1.y, red2);
+        if (broke) break;
+    }
+
+    if (tid < 64) {
+        double val = 0.0;
+        if (tid < a.n_obs) {
+            val = ok ? sh.src_w[tid] : NAN;
+            if (a.G) a.G[row * a.n_obs + tid] = val;
+        }
+        const double dlt = (tid < a.n_obs) ? val - a.y[tid] : 0.0;
+        const double s = wave_sum(dlt * dlt);
+        if (tid == 0) {
+            if (a.phi) a.phi[row] = ok ? s * a.inv2s2 : INFINITY;
+            if (a.iters) a.iters[row] = ok ? total : -1;
+            if (!ok) atomicOr(a.flags, SMC_FLAG_NOCONV);
+            if (a.stats) {
+                atomicAdd(&a.stats[0], (unsigned long long)total);
+                atomicAdd(&a.stats[1], (unsigned long long)sweeps);
+                atomicAdd(&a.stats[2], 1ull);
+                atomicAdd(&a.stats[3], (unsigned long long)napp);
+            }
+        }
+    }
+}
+
 template <typename T, bool ADJ>
 __global__ __launch_bounds__(1024) void cg_global(SolveArgs a, int NN) {
     __shared__ SolveShared sh;
@@ -1675,10 +2040,19 @@ __global__ __launch_bounds__(1024) void cg_global_dst(SolveArgs a, const _Float1
 }
 
 template <typename T, int NN>
+__global__ __launch_bounds__(1024) void cg_global_obs(SolveArgs a, const _Float16* __restrict__ Stab,
+                                                      const float* __restrict__ lamtab) {
+    __shared__ SolveShared sh;
+    cg_global_obs_body<T, NN>(a, blockIdx.x, a.obs, sh, reinterpret_cast<_Float16*>(g_mixed_smem), Stab, lamtab);
+}
+
+template <typename T, int NN>
 static hipError_t run_global_dst(int64_t N, const SolveArgs& a, const void* S, const float* lam, hipStream_t s) {
     const _Float16* Sh = reinterpret_cast<const _Float16*>(S);
     if (a.lam)
         cg_global_dst<T, NN, true><<<dim3((unsigned)N), dim3(1024), 0, s>>>(a, Sh, lam);
+    else if (!a.keep)
+        cg_global_obs<T, NN><<<dim3((unsigned)N), dim3(1024), 0, s>>>(a, Sh, lam);
     else
         cg_global_dst<T, NN, false><<<dim3((unsigned)N), dim3(1024), 0, s>>>(a, Sh, lam);
     return hipGetLastError();
@@ -1809,14 +2183,7 @@ __device__ __noinline__ void mixed_global(const SolveArgs& a, int64_t p, int n, 
     cg_global_body<T, false>(a, p, n, obs, g_mixed_sh);
 }
 
-template <typename T, int NN>
-__device__ __noinline__ void mixed_global_dst(const SolveArgs& a, int64_t p, const int32_t* obs, const void* S,
-                                              const float* lam) {
-    cg_global_body<T, false, true, NN>(a, p, NN, obs, g_mixed_sh, reinterpret_cast<_Float16*>(g_mixed_smem),
-                                       reinterpret_cast<const _Float16*>(S), lam);
-}
-
-template <int PREC, bool DST>
+template <int PREC>
 __global__ __launch_bounds__(1024) void solve_mixed_kernel(SolveArgs a, LevelTable lt,
                                                            const int32_t* __restrict__ level,
                                                            const int32_t* __restrict__ list, int64_t N,
@@ -1833,23 +2200,16 @@ __global__ __launch_bounds__(1024) void solve_mixed_kernel(SolveArgs a, LevelTab
         const int64_t p = __builtin_amdgcn_readfirstlane(list[item]);
         const int l = __builtin_amdgcn_readfirstlane(level[p]);
         const int n = (l >= 0 && l < lt.n_levels) ? lt.n[l] : 0;
-        const void* S = n ? lt.S[l] : nullptr;   // FP16 sine table
         if constexpr (PREC == SMC_FP32_REFINE) {
             if (n == 64)
-                mixed_onchip<float, 64, 4, DST>(a, p, lt.obs[l], S, lt.lam[l]);
+                mixed_onchip<float, 64, 4, false>(a, p, lt.obs[l], nullptr, nullptr);
             else if (n == 128)
-                mixed_onchip<float, 128, 16, DST>(a, p, lt.obs[l], S, lt.lam[l]);
-            else if (n == 256 && DST)
-                mixed_global_dst<float, 256>(a, p, lt.obs[l], S, lt.lam[l]);
+                mixed_onchip<float, 128, 16, false>(a, p, lt.obs[l], nullptr, nullptr);
             else if (n == 256)
                 mixed_global<float>(a, p, 256, lt.obs[l]);
         } else {
             if (n == 64)
                 mixed_onchip<double, 64, 4, false>(a, p, lt.obs[l], nullptr, nullptr);
-            else if (n == 128 && DST)
-                mixed_global_dst<double, 128>(a, p, lt.obs[l], S, lt.lam[l]);
-            else if (n == 256 && DST)
-                mixed_global_dst<double, 256>(a, p, lt.obs[l], S, lt.lam[l]);
             else if (n == 128 || n == 256)
                 mixed_global<double>(a, p, n, lt.obs[l]);
         }
@@ -1961,23 +2321,16 @@ hipError_t launch_stage_onchip(int n, int rows, const SolveArgs& a, const StageA
     return hipGetLastError();
 }
 
-hipError_t launch_solve_mixed(int prec, bool dst, int64_t N, const SolveArgs& a, const LevelTable& lt,
-                              const int32_t* level, const int32_t* list, unsigned long long* counters, int grid,
-                              hipStream_t s) {
+hipError_t launch_solve_mixed(int prec, int64_t N, const SolveArgs& a, const LevelTable& lt, const int32_t* level,
+                              const int32_t* list, unsigned long long* counters, int grid, hipStream_t s) {
     if (N <= 0) return hipSuccess;
     const unsigned g = (unsigned)(N < grid ? N : grid);
     if (prec == SMC_FP32_REFINE) {
-        if (dst)
-            solve_mixed_kernel<SMC_FP32_REFINE, true><<<dim3(g), dim3(1024), 0, s>>>(a, lt, level, list, N, counters);
-        else
-            solve_mixed_kernel<SMC_FP32_REFINE, false><<<dim3(g), dim3(1024), 0, s>>>(a, lt, level, list, N, counters);
+        solve_mixed_kernel<SMC_FP32_REFINE><<<dim3(g), dim3(1024), 0, s>>>(a, lt, level, list, N, counters);
     } else {
         SolveArgs b = a;
         b.tol_inner = 0.1 * a.tol64;
-        if (dst)
-            solve_mixed_kernel<SMC_FP64, true><<<dim3(g), dim3(1024), 0, s>>>(b, lt, level, list, N, counters);
-        else
-            solve_mixed_kernel<SMC_FP64, false><<<dim3(g), dim3(1024), 0, s>>>(b, lt, level, list, N, counters);
+        solve_mixed_kernel<SMC_FP64><<<dim3(g), dim3(1024), 0, s>>>(b, lt, level, list, N, counters);
     }
     return hipGetLastError();
 }
@@ -2019,7 +2372,7 @@ __global__ __launch_bounds__(1024) void solve_list_global(SolveArgs a, const int
     __shared__ SolveShared sh;
     const int64_t p = list_item(counters, lvl, list);
     if (p < 0) return;
-    cg_global_body<T, false, true, NN>(a, p, NN, obs, sh, reinterpret_cast<_Float16*>(g_mixed_smem), Stab, lamtab);
+    cg_global_obs_body<T, NN>(a, p, obs, sh, reinterpret_cast<_Float16*>(g_mixed_smem), Stab, lamtab);
 }
 
 // The particles with no grid (parked or out of range): the outputs of a rejected proposal.

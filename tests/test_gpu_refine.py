@@ -53,3 +53,30 @@ def test_observations_only(n, rows, prec, f):
         ref = observe(op, solve(op, synthesize(op, x[k], n), n), n)
         for got in (G[k].cpu().numpy(), K[k].cpu().numpy()):
             assert np.abs(got - ref).max() <= 1e-9 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("n,prec,tol_inner", [(256, 1, 1e-3), (256, 1, 1e-9), (256, 1, 1e-14), (256, 0, 1e-3),
+                                               (128, 0, 1e-3)])
+def test_observations_only_global(n, prec, tol_inner):
+    """The same for the solver with its vectors in memory.  An inner tolerance that FP32 cannot reach
+    takes more iterations than there are direction buffers (9 in FP32, 3 in FP64, whose one sweep
+    always does), so directions are folded into the correction on the way."""
+    from paper_2503_16028_amd import smc
+    print("[case] refine global", n, prec, tol_inner, flush=True)
+    d = json.load(open(golden("problem_t2.json")))
+    d.update(grids=[n], obs_den=n, obs=corners(n), y=[0.0] * 64, f=1.0, sigma=1.0)
+    op = OProblem(d)
+    N = 2
+    p = smc.Problem(d, N, tol64=1e-10, tol_inner=tol_inner, max_iter=200)
+    x = inputs.particles(N, op.K, 62)
+    xi = torch.tensor(x, device=DEV)
+    G = torch.full((N, 64), np.nan, dtype=torch.float64, device=DEV)
+    it = torch.zeros(N, dtype=torch.int32, device=DEV)
+    smc.smc_forward_batch(p, N, xi, None, prec, G, it)
+    torch.cuda.synchronize()
+    assert smc.smc_status_flags(p) == 0
+    if prec == 1 and tol_inner < 1e-10:   # past the nine buffers of the first sweep
+        assert (it.cpu().numpy() > 10).all()
+    for k in range(N):
+        ref = observe(op, solve(op, synthesize(op, x[k], n), n), n)
+        assert np.abs(G[k].cpu().numpy() - ref).max() <= 1e-9 * np.abs(ref).max()
