@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/smc.h"
 
 namespace smc {
@@ -345,6 +347,17 @@ hipError_t launch_propose(int64_t N, int K, const int32_t* active, const int32_t
 hipError_t launch_accept(int64_t N, int K, const MoveParams& q, const double* v, const double* logr,
                          const double* phinew, double* xi, double* phi, int32_t* n_acc, hipStream_t s);
 hipError_t prepare_kernels();
+hipError_t prepare_chain_kernels();
+// A whole stage of n_moves pCN-GM moves in one launch (k_chain.hip); n_acc is written, not added to.
+// The mixture and counters are read from q as the step kernels read them; no level map.
+bool chain_l2mix_supported(int K);
+hipError_t launch_chain_l2mix(int64_t N, int K, int n_moves, const MoveParams& q, const int32_t* slot,
+                              const double* sqrt_lam, const double* c, int T, double inv2s2, double* xi, double* phi,
+                              int32_t* n_acc, int32_t* flags, int n_cu, hipStream_t s);
+bool chain1d_supported(int n, int K, int M);
+hipError_t launch_chain1d(int64_t N, int K, int n, int n_moves, const MoveParams& q, const int32_t* slot,
+                          const double* sqrt_lam, const double* basis, const SolveArgs& a, double* xi, double* phi,
+                          int32_t* n_acc, int32_t* flags, int n_cu, hipStream_t s);
 hipError_t launch_l2mix_phi(int64_t N, int K, const double* sqrt_lam, const double* c, int T, double inv2s2,
                             const double* xi, double* phi, int32_t* iters, hipStream_t s);
 hipError_t launch_gm_draw(int64_t N, int K, const int32_t* slot, uint64_t seed, uint64_t ctr, int M, int kr,
