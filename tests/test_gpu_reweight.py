@@ -1,0 +1,118 @@
+"""Re-weighting, resampling and gather at the edges of their launches: one workgroup and many, whole and
+ragged tiles and chunks, a search that outlasts the launched passes (stall), weights written over the potentials,
+outputs on odd addresses, every row width.  Against the oracle with the bounds of the other tests of
+these calls: 1e-10 for the increment and the weights, exact indices and rows."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import inputs
+from oracle.resample import systematic
+from oracle.temper import temper
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def banner(*a):
+    print("[case]", *a, flush=True)
+    sys.stdout.flush()
+
+
+def t(a, dtype=torch.float64):
+    return torch.tensor(np.ascontiguousarray(a), dtype=dtype, device=DEV)
+
+
+def potentials(N, kind):
+    rng = np.random.default_rng(N)
+    if kind == "wide":                       # a search of about eleven passes
+        return np.exp(12.0 * rng.standard_normal(N) + 4.0)
+    if kind == "stall":
+        p = np.full(N, 1e308)
+        p[N // 2] = 0.0
+        return p
+    p = inputs.potentials(N, N)
+    if kind == "holes":
+        p[rng.random(N) < 0.4] = np.inf
+        p[0] = p[-1] = np.nan
+    if kind == "none":
+        p[:] = np.nan
+    return p
+
+
+@pytest.mark.parametrize("N,kind,place", [
+    (255, "plain", "apart"), (8064, "plain", "apart"), (8065, "plain", "apart"), (8065, "plain", "over"),
+    (9001, "wide", "apart"), (9001, "stall", "apart"), (9001, "none", "apart"), (9001, "holes", "odd"),
+    (262145, "holes", "apart"), (300001, "plain", "odd"), (1 << 20, "holes", "over")])
+def test_temper_launches(N, kind, place):
+    from paper_2503_16028_amd import smc
+    banner("temper", N, kind, place)
+    phi0 = potentials(N, kind)
+    room = torch.full((2 * N + 3,), 7.0, dtype=torch.float64, device=DEV)
+    phi = room[1:N + 1] if place == "odd" else room[:N]
+    phi.copy_(t(phi0))
+    W = phi if place == "over" else room[N + 1:2 * N + 1]
+    h, tau_new, lz = (torch.empty(1, dtype=torch.float64, device=DEV) for _ in range(3))
+    flags = torch.zeros(1, dtype=torch.int32, device=DEV)
+    smc.smc_temper(N, phi, t([0.1]), 0.5, h, tau_new, W, lz, flags)
+    Wg = W.cpu().numpy()
+    if kind == "none":
+        assert h.item() == 0.0 and tau_new.item() == 0.1 and lz.item() == -np.inf
+        assert not Wg.any() and flags.item() == smc.FLAG_NONFINITE
+        return
+    rh, rtau, rW, rlz, stalled = temper(phi0, 0.1, 0.5)
+    assert flags.item() == (smc.FLAG_STALL if stalled else 0)
+    assert h.item() == pytest.approx(rh, rel=1e-10, abs=1e-300) and tau_new.item() == pytest.approx(rtau, rel=1e-12)
+    assert lz.item() == pytest.approx(rlz, rel=1e-10, abs=1e-10)
+    pos = rW > 1e-290
+    assert np.array_equal(Wg[rW == 0.0], rW[rW == 0.0]) and np.abs(Wg[pos] / rW[pos] - 1).max() <= 1e-10
+    outside = [room[N + (place == "odd"):N + 1], room[2 * N + 1:]] if place != "over" else [room[N:]]
+    assert all((o == 7.0).all() for o in outside)
+
+
+@pytest.mark.parametrize("N", [8191, 8192, 8193, 10241, 100003, (1 << 20) + 1])
+@pytest.mark.parametrize("kind", ["dirichlet", "first", "last", "few", "bad"])
+def test_resample_launches(N, kind):
+    from paper_2503_16028_amd import smc
+    banner("resample", N, kind)
+    W = inputs.weights(N, N + 3, "dirichlet")
+    if kind in ("first", "last"):            # one end owns all but a sprinkling
+        W *= 1e-3
+        W[0 if kind == "first" else -1] += 1.0 - W.sum() - 1e-12
+    if kind == "few":                        # one output here and there, in the first entries too
+        W[:] = 0.0
+        W[::N // 7] = 0.1
+    if kind == "bad":
+        W[N - 1] = np.nan
+    u = inputs.u53(N)
+    room = torch.full((N + 2,), -5, dtype=torch.int32, device=DEV)
+    idx = room[1:N + 1]                      # 4-byte aligned only
+    flags = torch.zeros(1, dtype=torch.int32, device=DEV)
+    smc.smc_resample(N, t(W), u, idx, flags)
+    want = np.arange(N) if kind == "bad" else np.array(systematic(W, u))
+    assert np.array_equal(idx.cpu().numpy(), want) and room[0] == -5 and room[-1] == -5
+    assert flags.item() == (smc.FLAG_BADWEIGHTS if kind == "bad" else 0)
+
+
+@pytest.mark.parametrize("N,K", [(1, 1), (77, 17), (301, 32), (300, 66), (65, 130), (9, 258), (33, 1023), (66000, 34),
+                                 (33001, 128), (270001, 1)])
+@pytest.mark.parametrize("off", [0, 1])
+def test_gather_widths(N, K, off):
+    from paper_2503_16028_amd import smc
+    banner("gather", N, K, off)
+    rng = np.random.default_rng(K)
+    ii = rng.integers(0, N, N)
+    src, dst = (torch.full((N * K + 2,), 3.0, dtype=torch.float64, device=DEV) for _ in range(2))
+    xi, xo = src[off:off + N * K].view(N, K), dst[off:off + N * K].view(N, K)
+    xi.copy_(t(rng.standard_normal((N, K))))
+    phi, po = t(rng.standard_normal(N)), torch.empty(N, dtype=torch.float64, device=DEV)
+    idx = ii.copy()
+    idx[N // 2] = N                          # out of range: the row stays
+    smc.smc_gather(N, K, t(idx, torch.int32), xi, phi, xo, po)
+    want = xi[t(ii, torch.int64)]
+    want[N // 2] = 3.0
+    keep = np.arange(N) != N // 2
+    assert torch.equal(xo, want) and (dst[:off] == 3.0).all() and (dst[off + N * K:] == 3.0).all()
+    assert np.array_equal(po.cpu().numpy()[keep], phi.cpu().numpy()[ii][keep])
