@@ -67,7 +67,8 @@ struct Problem {
     unsigned long long* ws_counters = nullptr;   // [2] work and exit counters of the persistent solve
     double* ws_fit_d2 = nullptr;      // [n_max]   squared distance to the nearest seeded centre
     double* ws_fit_par = nullptr;     // [2][GM_PAR]  EM parameter blocks (ping-pong)
-    double* ws_fit_part = nullptr;    // [workgroups of 128 particles][MAX_M][1 + 2 MAX_KR]  partial sums
+    double* ws_fit_part = nullptr;    // [workgroups of 64 particles][MAX_M][1 + 2 MAX_KR]  partial sums
+    double* ws_fit_tiles = nullptr;   // [workgroups of 64 particles][kr][64]  the cloud's active coordinates
     int32_t* ws_fit_centers = nullptr;  // [MAX_M] seeded rows
     double* ws_mixtab = nullptr;      // [MAX_LEVELS][MIXTAB]  mixture tables of the proposal, per group
     int n_cu = 0;                // compute units of the device
@@ -367,6 +368,7 @@ struct FitWorkspace {
     double* d2;
     double* par;
     double* part;
+    double* tiles;   // may be nullptr
 };
 int64_t em_blocks(int64_t N);
 // Mixture fit on the library's static scratch array (no allocation), for up to STATIC_FIT_N

@@ -17,9 +17,11 @@
 // s_j = max(sum_n R_nj x_n^2 / N_j - m_j^2, floor).
 //
 // Layout of the work: every pass over the cloud runs on workgroups of 64 particles whose active
-// coordinates are first staged, transposed, in LDS (lanes read one row's coordinates together).
-// Reductions over the cloud leave one partial per workgroup in global memory and a one-workgroup
-// kernel adds them in workgroup order, so results never depend on scheduling.  Passing partials
+// coordinates are first staged, transposed, in LDS (lanes read one row's coordinates together).  They
+// are gathered from the rows once, into tiles of that shape: a gather touches a cache line per coordinate, 16
+// times the bytes, in each of the 60 passes of a fit (a caller without room for the tiles gathers each time).
+// Reductions over the cloud leave one partial per workgroup in global memory and the next kernel
+// adds them in a fixed order, so results never depend on scheduling.  Passing partials
 // between kernels, rather than through a last-workgroup handshake inside one kernel, avoids a
 // device-scope fence per workgroup (an L2 write-back on this part) in every iteration.
 #include <mutex>
@@ -37,9 +39,9 @@ constexpr int EM_P = 64;             // particles per workgroup
 constexpr int EM_LDX = EM_P + 1;     // padded row of the transposed particle slice
 
 // Parameter block (GM_PAR doubles, two of them ping-pong between iterations):
-//   logw [MAX_M], cst [MAX_M] (log w_j - sum_d log(2 pi s_jd) / 2), mean [MAX_M][MAX_KR],
+//   logw [MAX_M], [MAX_M] unused, mean [MAX_M][MAX_KR],
 //   var [MAX_M][MAX_KR], and for the E-step, coordinate-major: meanT [MAX_KR][MAX_M], ivT (1 / var).
-constexpr int PAR_LOGW = 0, PAR_CST = MAX_M, PAR_MEAN = 2 * MAX_M, PAR_VAR = PAR_MEAN + MAX_M * MAX_KR,
+constexpr int PAR_LOGW = 0, PAR_MEAN = 2 * MAX_M, PAR_VAR = PAR_MEAN + MAX_M * MAX_KR,
               PAR_MEANT = PAR_VAR + MAX_M * MAX_KR, PAR_IVT = PAR_MEANT + MAX_KR * MAX_M;
 static_assert(PAR_IVT + MAX_KR * MAX_M == GM_PAR, "parameter block layout");
 
@@ -57,24 +59,50 @@ __device__ __forceinline__ uint64_t qweight(double d2, int shift) {
     return (d2 > 0.0 && d2 < INFINITY) ? (uint64_t)floor(ldexp(d2, shift)) : 0ull;
 }
 
+// Where a pass finds the cloud: tiles of EM_P particles, coordinate-major [tile][kr][EM_P] and zero past N,
+// if there is room for them, else the rows themselves.
+struct Cloud {
+    const double* xi;
+    const int32_t* active;
+    const double* tiles;   // or nullptr
+    int K, kr;
+};
+
 // The workgroup's particles [n0, n0 + np) staged transposed: xs[d * EM_LDX + p] = x_{n0+p, d}
-// (zero beyond np).  Four waves; the 16 loads of a lane go out before the first store (rows
-// clamped into range, zeros selected afterwards).
-__device__ __forceinline__ void stage_rows(double* xs, const double* __restrict__ xi, const int32_t* __restrict__ active,
-                                           int K, int kr, int64_t n0, int np) {
-    constexpr int PER = EM_P / 4;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int k = active[lane < kr ? lane : 0];
+// (zero beyond np).  NT threads; a lane's loads go out before its first store (rows clamped into range,
+// zeros selected afterwards).
+template <int NT>
+__device__ __forceinline__ void stage_rows(double* xs, const Cloud& c, int64_t n0, int np) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (c.tiles) {
+        constexpr int PER = EM_P * MAX_KR / 2 / NT;
+        const double2* t = reinterpret_cast<const double2*>(c.tiles + n0 * c.kr);
+        const int end = c.kr * (EM_P / 2);
+        double2 v[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) v[i] = t[tid + i * NT < end ? tid + i * NT : 0];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int e = tid + i * NT, d = e / (EM_P / 2), p = 2 * (e % (EM_P / 2));
+            if (e < end) {
+                xs[d * EM_LDX + p] = v[i].x;
+                xs[d * EM_LDX + p + 1] = v[i].y;
+            }
+        }
+        return;
+    }
+    constexpr int W = NT / 64, PER = EM_P / W;
+    const int k = c.active[lane < c.kr ? lane : 0];
     double v[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-        const int p = wave + 4 * i;
-        v[i] = xi[(n0 + (p < np ? p : np - 1)) * K + k];
+        const int p = wave + W * i;
+        v[i] = c.xi[(n0 + (p < np ? p : np - 1)) * c.K + k];
     }
-    if (lane < kr) {
+    if (lane < c.kr) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int p = wave + 4 * i;
+            const int p = wave + W * i;
             xs[lane * EM_LDX + p] = p < np ? v[i] : 0.0;
         }
     }
@@ -108,53 +136,58 @@ __device__ __forceinline__ void publish(double* __restrict__ par, int M, int kr,
         par[PAR_MEANT + d * MAX_M + j] = m;
         par[PAR_IVT + d * MAX_M + j] = 1.0 / v;
     }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    for (int j = wave; j < M; j += nw) {   // one wave per component, lanes are coordinates
-        const double s = wave_sum(lane < kr ? log(2.0 * M_PI * va[j * MAX_KR + lane]) : 0.0);
-        if (lane == 0) {
-            par[PAR_LOGW + j] = lw[j];
-            par[PAR_CST + j] = lw[j] - 0.5 * s;
-        }
-    }
+    if ((int)threadIdx.x < M) par[PAR_LOGW + threadIdx.x] = lw[threadIdx.x];
 }
 
 }  // namespace
 
 // ------------------------------------------------------------------ seeding
 
+// The tiles of a cloud.
+__global__ __launch_bounds__(256) void gm_tiles_kernel(int64_t N, Cloud c, double* __restrict__ tiles) {
+    __shared__ double xs[MAX_KR * EM_LDX];
+    const int64_t n0 = (int64_t)blockIdx.x * EM_P;
+    stage_rows<256>(xs, c, n0, (int)(N - n0 < EM_P ? N - n0 : EM_P));
+    __syncthreads();
+    for (int e = threadIdx.x; e < c.kr * EM_P; e += 256) tiles[n0 * c.kr + e] = xs[(e / EM_P) * EM_LDX + e % EM_P];
+}
+
 // d2_n <- min(d2_n, |x_n - x_c|^2) for the last chosen centre c (d2_n <- |x_n - x_c|^2 when m = 1);
-// 64 particles per workgroup, one thread per particle after staging.
-__global__ __launch_bounds__(256) void kmpp_dist_kernel(int64_t N, int K, int kr, const int32_t* __restrict__ active,
-                                                        const double* __restrict__ xi,
-                                                        const int32_t* __restrict__ centers, int m,
+// 64 particles per workgroup, four threads (one per wave) per particle.  The halvings down to four sums
+// stay within the coordinates of one residue modulo 4, a thread's; the last two join the threads.
+__global__ __launch_bounds__(256) void kmpp_dist_kernel(int64_t N, Cloud c, const int32_t* __restrict__ centers, int m,
                                                         double* __restrict__ d2) {
 #pragma clang fp contract(off)
     __shared__ double xs[MAX_KR * EM_LDX];
-    __shared__ double cs[64];
+    __shared__ double cs[64], quarter[4][EM_P];
     const int64_t n0 = (int64_t)blockIdx.x * EM_P;
-    const int np = (int)(N - n0 < EM_P ? N - n0 : EM_P);
-    stage_rows(xs, xi, active, K, kr, n0, np);
+    const int kr = c.kr, np = (int)(N - n0 < EM_P ? N - n0 : EM_P);
+    stage_rows<256>(xs, c, n0, np);
     if (threadIdx.x < 64) {
         const int d = threadIdx.x;
-        cs[d] = d < kr ? xi[(int64_t)centers[m - 1] * K + active[d]] : 0.0;
+        cs[d] = d < kr ? c.xi[(int64_t)centers[m - 1] * c.K + c.active[d]] : 0.0;
     }
     __syncthreads();
-    const int p = threadIdx.x;
-    if (p >= np) return;
-    double s[32];
+    const int p = threadIdx.x & 63, r = threadIdx.x >> 6;
+    double s[8];   // of d = r + 4 i
 #pragma unroll
-    for (int d = 0; d < 32; ++d) {
+    for (int i = 0; i < 8; ++i) {
+        const int d = r + 4 * i;
         const double ta = xs[(d < kr ? d : 0) * EM_LDX + p] - cs[d];
         const double tb = xs[(d + 32 < kr ? d + 32 : 0) * EM_LDX + p] - cs[d + 32];
         const double a = d < kr ? ta * ta : 0.0, b = d + 32 < kr ? tb * tb : 0.0;
-        s[d] = a + b;
+        s[i] = a + b;
     }
 #pragma unroll
-    for (int w = 16; w >= 1; w >>= 1)
+    for (int w = 4; w >= 1; w >>= 1)
 #pragma unroll
-        for (int d = 0; d < w; ++d) s[d] = s[d] + s[d + w];
+        for (int i = 0; i < w; ++i) s[i] = s[i] + s[i + w];
+    quarter[r][p] = s[0];
+    __syncthreads();
+    if (r > 0 || p >= np) return;
+    const double t = (quarter[0][p] + quarter[2][p]) + (quarter[1][p] + quarter[3][p]);
     const int64_t n = n0 + p;
-    d2[n] = (m == 1) ? s[0] : fmin(d2[n], s[0]);
+    d2[n] = (m == 1) ? t : fmin(d2[n], t);
 }
 
 // Centre m from d2 (m >= 1) or uniformly (m = 0); one workgroup of 1024 threads.
@@ -223,20 +256,18 @@ __global__ __launch_bounds__(1024) void kmpp_pick_kernel(int64_t N, int m, uint6
 
 // Column sums of x - c and (x - c)^2 per workgroup (c = the first seeded row, a shift that keeps
 // the one-pass variance accurate): part[b][0..kr) and part[b][kr..2kr).
-__global__ __launch_bounds__(256) void gm_colstats_kernel(int64_t N, int K, int kr, const int32_t* __restrict__ active,
-                                                          const double* __restrict__ xi,
-                                                          const int32_t* __restrict__ centers,
+__global__ __launch_bounds__(256) void gm_colstats_kernel(int64_t N, Cloud cloud, const int32_t* __restrict__ centers,
                                                           double* __restrict__ part) {
     __shared__ double xs[MAX_KR * EM_LDX];
     __shared__ double red[4][2][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t n0 = (int64_t)blockIdx.x * EM_P;
-    const int np = (int)(N - n0 < EM_P ? N - n0 : EM_P);
-    stage_rows(xs, xi, active, K, kr, n0, np);
+    const int kr = cloud.kr, np = (int)(N - n0 < EM_P ? N - n0 : EM_P);
+    stage_rows<256>(xs, cloud, n0, np);
     __syncthreads();
     double s1 = 0.0, s2 = 0.0;
     if (lane < kr) {
-        const double c = xi[(int64_t)centers[0] * K + active[lane]];
+        const double c = cloud.xi[(int64_t)centers[0] * cloud.K + cloud.active[lane]];
         for (int p = 16 * wave; p < 16 * wave + 16 && p < np; ++p) {
             const double t = xs[lane * EM_LDX + p] - c;
             s1 += t;
@@ -280,38 +311,54 @@ __global__ __launch_bounds__(256) void gm_start_kernel(int64_t N, int K, int kr,
 // E-step and the M-step's partial sums of one workgroup: part[b][j] = {sum R, sum R x, sum R x^2}
 // over its 64 particles (E = 1 + 2 kr entries per component).  MB >= M components are computed
 // without branches; those beyond M are masked out of the responsibilities and never written.
+// Eight waves, so that each of the serial chains (the coordinates of a distance, the components of a
+// particle's normalisation, the particles of a sum) is an eighth of its length: with 64 workgroups for
+// 4096 particles the kernel is all latency.  4096 particles, M = 8, 64 modes: 15.3 -> 9.2 us.
+constexpr int EM_NT = 512, EM_W = EM_NT / 64;
 template <int MB>
-__global__ __launch_bounds__(256) void em_partial_kernel(int64_t N, int K, int kr, const int32_t* __restrict__ active,
-                                                         const double* __restrict__ xi, int M,
-                                                         const double* __restrict__ par,
-                                                         double* __restrict__ part) {
-    extern __shared__ double smem[];
+struct EmLds {   // in doubles
+    static constexpr int SP = MAX_KR * EM_LDX;         // [EM_W][MB][EM_P]  partial distances, then ll and exp(ll - max)
+    static constexpr int R = SP + EM_W * MB * EM_P;    // [EM_P][MB]  responsibilities
+    static constexpr int PM = R + EM_P * MB;           // [kr][MB]  means, coordinate-major
+    static constexpr int PV = PM + MAX_KR * MB;        // [kr][MB]  1 / variances
+    static constexpr int PC = PV + MAX_KR * MB;        // [MB]  log w_j - sum_d log(2 pi s_jd) / 2
+    static constexpr int WPART = EM_W * MB * (1 + 2 * MAX_KR);   // over all of it: [EM_W][MB][E]
+    static constexpr size_t BYTES = sizeof(double) * (size_t)(PC + MB > WPART ? PC + MB : WPART);
+};
+template <int MB>
+__global__ __launch_bounds__(EM_NT) void em_partial_kernel(int64_t N, Cloud c, int M, const double* __restrict__ par,
+                                                           double* __restrict__ part) {
+    extern __shared__ __align__(16) double smem[];
+    using L = EmLds<MB>;
     double* xs = smem;                         // [kr][EM_LDX]  the workgroup's particles, transposed
-    double* sp = xs + MAX_KR * EM_LDX;         // [4][EM_P][MAX_M]  quarter sums of the E-step, then R
-    double* pm = sp + 4 * EM_P * MAX_M;        // [kr][MB]  means, coordinate-major
-    double* pv = pm + MAX_KR * MB;             // [kr][MB]  1 / variances
-    double* pc = pv + MAX_KR * MB;             // [MB]      log w_j - sum_d log(2 pi s_jd) / 2
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int E = 1 + 2 * kr;
+    double* sp = smem + L::SP;
+    double* rs = smem + L::R;
+    double* pm = smem + L::PM;
+    double* pv = smem + L::PV;
+    double* pc = smem + L::PC;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kr = c.kr, E = 1 + 2 * kr;
     const int64_t n0 = (int64_t)blockIdx.x * EM_P;
     const int np = (int)(N - n0 < EM_P ? N - n0 : EM_P);
-    for (int i = tid; i < kr * MB; i += 256) {   // the parameters go out with the rows' loads
+    for (int i = tid; i < kr * MB; i += EM_NT) {   // the parameters go out with the particles' loads
         pm[i] = par[PAR_MEANT + (i / MB) * MAX_M + i % MB];
         pv[i] = par[PAR_IVT + (i / MB) * MAX_M + i % MB];
     }
-    if (tid < MB) pc[tid] = par[PAR_CST + tid];
-    stage_rows(xs, xi, active, K, kr, n0, np);
+    stage_rows<EM_NT>(xs, c, n0, np);
+    for (int j = wave; j < M; j += EM_W) {
+        const double s = wave_sum(lane < kr ? log(2.0 * M_PI * par[PAR_VAR + j * MAX_KR + lane]) : 0.0);
+        if (lane == 0) pc[j] = par[PAR_LOGW + j] - 0.5 * s;
+    }
     __syncthreads();
 
-    {   // E-step, a quarter of the coordinates per thread (wave); parameters are LDS broadcasts
-        const int p = tid & (EM_P - 1), h = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const int dlo = h * kr / 4, dhi = (h + 1) * kr / 4;
+    {   // distances, an eighth of the coordinates per wave, lanes are particles; parameters are LDS broadcasts
+        const int dlo = wave * kr / EM_W, dhi = (wave + 1) * kr / EM_W;
         double s[MB];
 #pragma unroll
         for (int j = 0; j < MB; ++j) s[j] = 0.0;
 #pragma unroll 4
         for (int d = dlo; d < dhi; ++d) {
-            const double x = xs[d * EM_LDX + p];
+            const double x = xs[d * EM_LDX + lane];
 #pragma unroll
             for (int j = 0; j < MB; ++j) {
                 const double t = x - pm[d * MB + j];
@@ -319,93 +366,111 @@ __global__ __launch_bounds__(256) void em_partial_kernel(int64_t N, int K, int k
             }
         }
 #pragma unroll
-        for (int j = 0; j < MB; ++j) sp[(h * EM_P + p) * MAX_M + j] = s[j];
-    }
-    __syncthreads();
-    if (tid < EM_P) {
-        const int p = tid;
-        double ll[MB];
-        double mx = -INFINITY;
-#pragma unroll
-        for (int j = 0; j < MB; ++j) {
-            const double q = ((sp[p * MAX_M + j] + sp[(EM_P + p) * MAX_M + j]) + sp[(2 * EM_P + p) * MAX_M + j]) +
-                             sp[(3 * EM_P + p) * MAX_M + j];
-            const double v = pc[j] - 0.5 * q;
-            ll[j] = j < M ? v : -INFINITY;
-            mx = fmax(mx, ll[j]);
-        }
-        double se = 0.0;
-#pragma unroll
-        for (int j = 0; j < MB; ++j) se += j < M ? exp(ll[j] - mx) : 0.0;
-        const double lse = mx + log(se);
-#pragma unroll
-        for (int j = 0; j < MB; ++j) sp[p * MAX_M + j] = (p < np && j < M) ? exp(ll[j] - lse) : 0.0;
+        for (int j = 0; j < MB; ++j) sp[(wave * MB + j) * EM_P + lane] = s[j];
     }
     __syncthreads();
 
-    // M-step partial sums: wave w takes particles [16 w, 16 w + 16); lanes are coordinates
+    // responsibilities: wave w takes components w, w + 8 (an exponential per particle and component)
+    constexpr int JW = (MB + EM_W - 1) / EM_W;
+    double ll[JW];
+#pragma unroll
+    for (int i = 0; i < JW; ++i) {
+        const int j = wave + i * EM_W;
+        ll[i] = -INFINITY;
+        if (j < MB) {
+            double q = 0.0;
+#pragma unroll
+            for (int w = 0; w < EM_W; ++w) q += sp[(w * MB + j) * EM_P + lane];
+            if (j < M) ll[i] = pc[j] - 0.5 * q;
+            sp[j * EM_P + lane] = ll[i];   // of the first wave's slot: read by this thread alone until the barrier
+        }
+    }
+    __syncthreads();
+    double mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < MB; ++j) mx = fmax(mx, sp[j * EM_P + lane]);
+#pragma unroll
+    for (int i = 0; i < JW; ++i) {
+        const int j = wave + i * EM_W;
+        ll[i] = j < M ? exp(ll[i] - mx) : 0.0;
+        if (j < MB) sp[(MB + j) * EM_P + lane] = ll[i];
+    }
+    __syncthreads();
+    double se = 0.0;
+#pragma unroll
+    for (int j = 0; j < MB; ++j) se += sp[(MB + j) * EM_P + lane];
+#pragma unroll
+    for (int i = 0; i < JW; ++i) {
+        const int j = wave + i * EM_W;
+        if (j < MB) rs[lane * MB + j] = (lane < np && j < M) ? ll[i] / se : 0.0;
+    }
+    __syncthreads();
+
+    // M-step partial sums: wave w takes particles [8 w, 8 w + 8); lanes are coordinates
     double a1[MB], a2[MB], a0 = 0.0;
 #pragma unroll
     for (int j = 0; j < MB; ++j) a1[j] = a2[j] = 0.0;
 #pragma unroll 4
-    for (int p = 16 * wave; p < 16 * wave + 16; ++p) {
+    for (int p = EM_P / EM_W * wave; p < EM_P / EM_W * (wave + 1); ++p) {
         const double x = lane < kr ? xs[lane * EM_LDX + p] : 0.0, xx = x * x;
 #pragma unroll
         for (int j = 0; j < MB; ++j) {
-            const double r = sp[p * MAX_M + j];
+            const double r = rs[p * MB + j];
             a1[j] += r * x;
             a2[j] += r * xx;
         }
-        if (lane < M) a0 += sp[p * MAX_M + lane];
+        if (lane < MB) a0 += rs[p * MB + lane];
     }
-    __syncthreads();                       // xs and sp are reused for the per-wave partials below
-    double* wpart = smem;                  // [4][MAX_M][E]
+    __syncthreads();                       // everything above is reused for the per-wave partials below
+    double* wpart = smem;                  // [EM_W][MB][E]
 #pragma unroll
     for (int j = 0; j < MB; ++j) {
         if (j < M && lane < kr) {
-            wpart[(wave * MAX_M + j) * E + 1 + lane] = a1[j];
-            wpart[(wave * MAX_M + j) * E + 1 + kr + lane] = a2[j];
+            wpart[(wave * MB + j) * E + 1 + lane] = a1[j];
+            wpart[(wave * MB + j) * E + 1 + kr + lane] = a2[j];
         }
     }
-    if (lane < M) wpart[(wave * MAX_M + lane) * E] = a0;
+    if (lane < M) wpart[(wave * MB + lane) * E] = a0;
     __syncthreads();
     double* bpart = part + (int64_t)blockIdx.x * MAX_M * E;
-    for (int i = tid; i < M * E; i += 256) {
-        const int j = i / E, e = i % E;
+    for (int i = tid; i < M * E; i += EM_NT) {
         double s = 0.0;
-        for (int w = 0; w < 4; ++w) s += wpart[(w * MAX_M + j) * E + e];
-        bpart[j * E + e] = s;
+#pragma unroll
+        for (int w = 0; w < EM_W; ++w) s += wpart[w * MB * E + i];
+        bpart[i] = s;
     }
 }
 
-// M-step of component j = blockIdx.x: its partials from B workgroups added in workgroup order,
-// then its entries of the next parameter block.  One workgroup per component.
-__global__ __launch_bounds__(256) void em_final_kernel(int64_t N, int kr, double var_floor, int B,
-                                                       const double* __restrict__ part, double* __restrict__ par) {
-    __shared__ double tot[1 + 2 * MAX_KR];
-    const int tid = threadIdx.x, lane = tid & 63, j = blockIdx.x;
-    const int E = 1 + 2 * kr;
-    if (tid < E) tot[tid] = ordered_sum(part + (int64_t)j * E, B, (int64_t)MAX_M * E, tid);
+// M-step of component j = blockIdx.x, coordinates 15 blockIdx.y + 0 .. 14: their two sums and the sum
+// of R (31 columns) over B workgroups, 32 threads to a column, then the entries of the next parameter
+// block.  One workgroup per component, a thread to a column, took 5.8 us at 64 workgroups of partials (and a
+// chain of all of them for a large cloud); now 4.1.
+constexpr int EM_COLS = 15;
+__global__ __launch_bounds__(1024) void em_final_kernel(int64_t N, int kr, double var_floor, int B,
+                                                        const double* __restrict__ part, double* __restrict__ par) {
+    __shared__ double red[32][33];
+    const int tid = threadIdx.x, col = tid & 31, g = tid >> 5, j = blockIdx.x;
+    const int E = 1 + 2 * kr, d = (int)blockIdx.y * EM_COLS + (col - 1) % EM_COLS;   // col 0: the sum of R
+    const bool second = col > EM_COLS, use = col == 0 || (col <= 2 * EM_COLS && d < kr);
+    const int e = col == 0 || !use ? 0 : second ? 1 + kr + d : 1 + d;
+    const double* a = part + (int64_t)j * E + e;
+    double s = 0.0;
+#pragma unroll 4
+    for (int b = g; b < B; b += 32) s += a[(int64_t)b * MAX_M * E];
+    red[g][col] = s;
     __syncthreads();
-    const double nk = tot[0] + 1e-300;
-    const double lw = log(nk / (double)N);
-    if (tid < 64) {   // wave 0: lanes are coordinates
-        const int d = lane;
-        double lg = 0.0;
-        if (d < kr) {
-            const double m = tot[1 + d] / nk;
-            const double v = fmax(tot[1 + kr + d] / nk - m * m, var_floor);
-            par[PAR_MEAN + j * MAX_KR + d] = m;
-            par[PAR_VAR + j * MAX_KR + d] = v;
-            par[PAR_MEANT + d * MAX_M + j] = m;
-            par[PAR_IVT + d * MAX_M + j] = 1.0 / v;
-            lg = log(2.0 * M_PI * v);
-        }
-        const double s = wave_sum(lg);
-        if (lane == 0) {
-            par[PAR_LOGW + j] = lw;
-            par[PAR_CST + j] = lw - 0.5 * s;
-        }
+    if (tid >= 64) return;
+    s = 0.0;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) s += red[i][col];
+    const double nk = __shfl(s, 0, 64) + 1e-300, s2 = __shfl(s, (col + EM_COLS) & 31, 64);
+    if (tid == 0 && blockIdx.y == 0) par[PAR_LOGW + j] = log(nk / (double)N);
+    if (tid >= 1 && tid <= EM_COLS && d < kr) {
+        const double m = s / nk, v = fmax(s2 / nk - m * m, var_floor);
+        par[PAR_MEAN + j * MAX_KR + d] = m;
+        par[PAR_VAR + j * MAX_KR + d] = v;
+        par[PAR_MEANT + d * MAX_M + j] = m;
+        par[PAR_IVT + d * MAX_M + j] = 1.0 / v;
     }
 }
 
@@ -427,12 +492,6 @@ __global__ void gm_output_kernel(int M, int kr, const double* __restrict__ par, 
     }
 }
 
-static size_t em_smem_bytes() {
-    constexpr size_t work = MAX_KR * EM_LDX + 4 * EM_P * MAX_M + 2 * MAX_KR * MAX_M + MAX_M,
-                     wpart = 4 * MAX_M * (1 + 2 * MAX_KR);
-    return sizeof(double) * (work > wpart ? work : wpart);
-}
-
 int64_t em_blocks(int64_t N) { return (N + EM_P - 1) / EM_P; }
 
 namespace {
@@ -441,24 +500,29 @@ hipError_t gm_fit(int64_t N, int K, int kr, const int32_t* active, const double*
                   int32_t* centers, double* logw, double* mean, double* scale, hipStream_t s) {
     if (N <= 0) return hipSuccess;
     const unsigned B = (unsigned)em_blocks(N);
+    Cloud c{xi, active, nullptr, K, kr};
+    if (w.tiles) {
+        gm_tiles_kernel<<<B, 256, 0, s>>>(N, c, w.tiles);
+        c.tiles = w.tiles;
+    }
     kmpp_pick_kernel<<<1, 1024, 0, s>>>(N, 0, seed, ctr, ctr_dev, w.d2, centers);
     for (int m = 1; m < M; ++m) {
-        kmpp_dist_kernel<<<B, 256, 0, s>>>(N, K, kr, active, xi, centers, m, w.d2);
+        kmpp_dist_kernel<<<B, 256, 0, s>>>(N, c, centers, m, w.d2);
         kmpp_pick_kernel<<<1, 1024, 0, s>>>(N, m, seed, ctr, ctr_dev, w.d2, centers);
     }
-    gm_colstats_kernel<<<B, 256, 0, s>>>(N, K, kr, active, xi, centers, w.part);
+    gm_colstats_kernel<<<B, 256, 0, s>>>(N, c, centers, w.part);
     gm_start_kernel<<<1, 256, 0, s>>>(N, K, kr, active, xi, centers, M, var_floor, (int)B, w.part, w.par);
-    const size_t lds = em_smem_bytes();
+    const dim3 fin(M, (kr + EM_COLS - 1) / EM_COLS);
     for (int it = 0; it < iters; ++it) {
         const double* pin = w.par + (it & 1) * GM_PAR;
         double* pout = w.par + ((it + 1) & 1) * GM_PAR;
         if (M <= 4)
-            em_partial_kernel<4><<<B, 256, lds, s>>>(N, K, kr, active, xi, M, pin, w.part);
+            em_partial_kernel<4><<<B, EM_NT, EmLds<4>::BYTES, s>>>(N, c, M, pin, w.part);
         else if (M <= 8)
-            em_partial_kernel<8><<<B, 256, lds, s>>>(N, K, kr, active, xi, M, pin, w.part);
+            em_partial_kernel<8><<<B, EM_NT, EmLds<8>::BYTES, s>>>(N, c, M, pin, w.part);
         else
-            em_partial_kernel<16><<<B, 256, lds, s>>>(N, K, kr, active, xi, M, pin, w.part);
-        em_final_kernel<<<M, 256, 0, s>>>(N, kr, var_floor, (int)B, w.part, pout);
+            em_partial_kernel<16><<<B, EM_NT, EmLds<16>::BYTES, s>>>(N, c, M, pin, w.part);
+        em_final_kernel<<<fin, 1024, 0, s>>>(N, kr, var_floor, (int)B, w.part, pout);
     }
     gm_output_kernel<<<1, 256, 0, s>>>(M, kr, w.par + (iters & 1) * GM_PAR, logw, mean, scale);
     return hipGetLastError();
@@ -530,17 +594,16 @@ hipError_t launch_gm_fit_static(int64_t N, int K, int kr, const int32_t* active,
     double* base = nullptr;
     const hipError_t e = static_fit_scratch(&base);
     if (e != hipSuccess) return e;
-    FitWorkspace w{base, base + STATIC_FIT_N, base + STATIC_FIT_N + 2 * GM_PAR};
+    FitWorkspace w{base, base + STATIC_FIT_N, base + STATIC_FIT_N + 2 * GM_PAR, nullptr};
     int32_t* rows = centers ? centers : (int32_t*)(base + STATIC_FIT_N + 2 * GM_PAR + STATIC_FIT_PART);
     return launch_gm_fit(N, K, kr, active, xi, M, iters, var_floor, seed, ctr, w, rows, logw, mean, scale, s);
 }
 
 hipError_t prepare_gmfit_kernels() {
     const hipFuncAttribute A = hipFuncAttributeMaxDynamicSharedMemorySize;
-    const int bytes = (int)em_smem_bytes();
-    hipError_t e = hipFuncSetAttribute((const void*)em_partial_kernel<4>, A, bytes);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)em_partial_kernel<8>, A, bytes);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)em_partial_kernel<16>, A, bytes);
+    hipError_t e = hipFuncSetAttribute((const void*)em_partial_kernel<4>, A, (int)EmLds<4>::BYTES);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)em_partial_kernel<8>, A, (int)EmLds<8>::BYTES);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)em_partial_kernel<16>, A, (int)EmLds<16>::BYTES);
     return e;
 }
 
