@@ -1317,6 +1317,110 @@ __device__ __forceinline__ vec4_t<T> fma4(T a, vec4_t<T> b, vec4_t<T> c) {
     return o;
 }
 
+// The transform that ends in the next search direction, p = z + (r.z / rz) pc (p = z without pc), and
+// returns r.z.  With S symmetric, r.z = r.S (S r S) / lam S is the sum of (S r S)^2 / lam over the
+// modes, known half way, in FP32 from the matrix units' accumulators: the residual is not read again, and z, with beta in
+// hand before its last product, is neither written nor read.  A residual that overflows the staged scale gives a
+// sum that is not finite: p is then left alone.
+// Inlined (a call saves a third of the registers to memory), with the thread's index opaque, so that no
+// address of it is kept through the loop over the iterations.
+__shared__ double g_dst_red[16];
+__shared__ __align__(16) float g_dst_lam[256];   // lam, staged by the kernel
+template <int NN, typename T>
+__device__ __forceinline__ double dstg_direction(const T* r, T* p, const T* pc, double rz, const _Float16* S, int staged,
+                                                 int ex) {
+    typedef T V4 __attribute__((ext_vector_type(4)));
+    constexpr int LD = NN + 8, KS = NN / 32, NBT = NN / 16, WPC = 16 / NBT, RT = NBT / WPC;
+    _Float16* X = reinterpret_cast<_Float16*>(g_mixed_smem);
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int lr = lane & 15, lk = lane >> 4, cb = wave % NBT, ra0 = (wave / NBT) * RT;
+    const float unsc = ldexpf(1.0f, ex);
+    const gcbp pcB = uniform_base(pc), pB = uniform_base(p), SB = uniform_base(S);
+    hf8 sB[KS];   // as in dstg_apply
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+        sB[ks] = at_off<hf8>(SB, (uint32_t)(((16 * cb + lr) * NN + 32 * ks + 8 * lk) * 2));
+    if (!staged) {   // X = fp16(r 2^-ex), row-major
+        const T s = (T)ldexpf(1.0f, -ex);
+        const gcbp rB = uniform_base(r);
+#pragma unroll 1
+        for (int k = 4 * tid; k < NN * NN; k += 4096) {
+            const V4 u = at_off<V4>(rB, (uint32_t)(k * sizeof(T)));
+            hf4 v;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) v[m] = (_Float16)(float)(u[m] * s);
+            *reinterpret_cast<hf4*>(X + (k / NN) * LD + k % NN) = v;
+        }
+    }
+    __syncthreads();
+    const float lam_c = g_dst_lam[16 * cb + lr];
+    double sum = 0.0;
+    T beta = T(0);
+#pragma unroll 1
+    for (int step = 0; step < 4; ++step) {
+        hf4 out[RT];
+        uint32_t at = (uint32_t)(((16 * cb + lr) * NN + 16 * ra0 + 4 * lk) * sizeof(T));
+        asm volatile("" : "+v"(at));
+        if (step == 3) {
+            sum = 0.0;
+#pragma unroll
+            for (int w = 0; w < 16; ++w) sum += g_dst_red[w];
+            sum = uniform(ldexp(sum, 2 * ex));
+            if (!(fabs(sum) < INFINITY)) break;
+            beta = pc ? (T)(sum / rz) : T(0);
+        }
+        float part = 0.f;
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {   // P[i][j] = sum_k X[i][k] S[k][j], i in row tile ra, j in cb
+            const int ra = ra0 + i;
+            f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                acc = mfma_f16(*reinterpret_cast<const hf8*>(X + (16 * ra + lr) * LD + 32 * ks + 8 * lk), sB[ks], acc);
+            if (step == 1) {
+                const f4 lam_r = *reinterpret_cast<const f4*>(g_dst_lam + 16 * ra + 4 * lk);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float y = acc[v] * __builtin_amdgcn_rcpf(lam_r[v] + lam_c);
+                    part = __builtin_fmaf(acc[v], y, part);
+                    acc[v] = y;
+                }
+            }
+            if (step == 3) {   // z[j][i] = P[i][j]
+                constexpr uint32_t NEXT = 16 * sizeof(T);   // from row tile to row tile
+                V4 z;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) z[v] = (T)(acc[v] * unsc);
+                if (pc) {
+                    const V4 b = at_off<V4>(pcB + i * NEXT, at);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) z[v] = fma_t(beta, b[v], z[v]);
+                }
+                put_off<V4>(pB + i * NEXT, at, z);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) out[i][v] = (_Float16)acc[v];
+            }
+            if (i % 2 == 1) asm volatile("" ::: "memory");   // fragments of at most two tiles in flight
+        }
+        if (step < 3) {
+            if (step == 1) {
+                const double w = wave_sum((double)part);
+                if (lane == 0) g_dst_red[wave] = w;
+            }
+            __syncthreads();   // every wave has finished reading X
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+                *reinterpret_cast<hf4*>(X + (16 * cb + lr) * LD + 16 * (ra0 + i) + 4 * lk) = out[i];
+            __syncthreads();
+        }
+    }
+    __syncthreads();   // p complete for every thread of the workgroup, and X free
+    return sum;
+}
+
 __global__ __launch_bounds__(1024) void dst256_apply_kernel(const float* __restrict__ rin, float* __restrict__ zout,
                                                             const _Float16* __restrict__ Stab,
                                                             const float* __restrict__ lamtab) {
@@ -1645,19 +1749,27 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
 // reaches 4.7).  An iteration
 //   - keeps its search direction in a buffer of its own instead of adding it to x: the correction is
 //     sum alpha_k p_k once at the end of the sweep (directions are folded into x when the buffers are
-//     used up), so x and p are not read and x is not written per iteration: 10 vector passes, were 13;
-//   - takes the horizontal neighbours from the adjacent lanes.
+//     used up), so x is not touched per iteration;
+//   - gets its direction from the transform (dstg_direction), which has r.z before its last product, so z
+//     stays in registers;
+//   - keeps q = A p in registers from the product with A to the residual's update (the same thread, the
+//     same nodes);
+//   - runs down bands of rows, the neighbours above and below carried in registers, the horizontal ones taken
+//     from the adjacent lanes;
+// and moves p twice, r twice, t and the direction before: 6 vector passes, where cg_global_body has 13 and a
+// version with z and q in memory 10.
 // A refinement step rounds dx = D^{-1/2} y to T and updates the FP64 residual, as strip_refine does; the
 // FP64 passes run down columns, the vertical neighbours carried in registers.  The passes over the
 // vectors keep a few loads in flight per thread and leave the rest to the sixteen waves: unrolled
-// further they spill, and scratch traffic is what this solver can least afford.  Measured: 1024 solves
-// at 256^2 in FP32 10.70 -> 7.73 ms, 32 solves 1.45 -> 0.93 ms, 1001 at 128^2 in FP64 2.77 -> 2.63 ms.
-// Vector slots of a particle's row of a.vec (7 n^2 doubles): t, r, q, z, then the directions; FP32 has
+// further they spill, and scratch traffic is what this solver can least afford.  Measured, with 13, 10 and
+// 6 passes: 1024 solves at 256^2 in FP32 10.70, 7.73 and 5.4 ms; 32 solves 1.45, 0.93 and
+// 0.72; 1001 at 128^2 in FP64 2.77, 2.63 and 1.90.
+// Vector slots of a particle's row of a.vec (7 n^2 doubles): t, r, q, then the directions; FP32 has
 // the last one for x, FP64 keeps x in a.aux.
 template <typename T, int NN>
 struct GlobalSlots {
     static constexpr bool F32 = std::is_same<T, float>::value;
-    static constexpr int NP = F32 ? 9 : 3;   // direction buffers
+    static constexpr int NP = F32 ? 10 : 4;   // direction buffers
 };
 
 // four consecutive values of a row that starts on any element
@@ -1810,6 +1922,13 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
     using T4 = vec4_t<T>;
     using SD = typename std::conditional<F32, float, double>::type;   // as cg_global_body keeps D^{-1/2}
     const int tid = threadIdx.x, c = tid % NN, b = tid / NN;
+    // the iteration's share of a thread: four columns from cc, a band of RB rows from g0
+    constexpr int RB = nodes / 4096;
+    constexpr bool QREG = RB * 4 * sizeof(T) <= 256;   // q in registers (not FP64 at 256^2)
+    constexpr int QU = QREG ? RB : 2;
+    constexpr uint32_t ROW = NN * sizeof(T);
+    typedef T V4 __attribute__((ext_vector_type(4)));
+    const int cc = 4 * (tid % (NN / 4)), g0 = tid / (NN / 4) * RB, k0 = g0 * NN + cc;
     const double* e = a.e + row * a.e_stride;
     double* r64 = a.x64 + row * a.x_stride;
     SD* sd = reinterpret_cast<SD*>(a.sd + row * a.sd_stride);
@@ -1817,8 +1936,7 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
     T* tv = vb;
     T* rv = vb + nodes;
     T* qv = vb + 2 * nodes;
-    T* zv = vb + 3 * nodes;
-    T* pb = vb + 4 * nodes;   // NP directions
+    T* pb = vb + 3 * nodes;   // NP directions
     T* xv = F32 ? vb + 13 * nodes : reinterpret_cast<T*>(a.aux + row * a.aux_stride);
     const float* w0 = lamtab + NN;
     double* red1 = sh.red1;
@@ -1826,6 +1944,7 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
     __shared__ T alphas[NP];
     auto interior = [](int g, int cc) { return cc < NN - 1 && g < NN - 1; };
 
+    if (tid < NN) g_dst_lam[tid] = lamtab[tid];
     if (tid < a.n_obs) {   // the observed nodes and the running sums of their corrections
         const int node = obs[tid];
         const int jj = node / NP1, ii = node % NP1;
@@ -1852,16 +1971,10 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
         const double target = red * red * rr;
         bool broke = false, have_x = false;
         int np = 0;   // directions not yet in x
-        bool w_first = W0 && sweep == 0;
-        double rz;
-        if (w_first) {
-            rz = rw;
-        } else {
-            rz = block_sum<NW>(dstg_precondition<NN, T>(rv, pb, Stab, lamtab, 0, norm_exponent(rr) + 3, 1), red2);
-            ++napp;
-        }
-        const T* pc = pb;   // the current direction (FP32: w0's table at first)
-        if constexpr (W0) pc = w_first ? reinterpret_cast<const T*>(w0) : pb;
+        const T* pc = nullptr;   // the current direction (FP32: w0's table at first)
+        double rz = 0.0, pq = 0.0;
+        bool w_now = false;      // it is w0
+        int ex = norm_exponent(rr) + 3;   // the scale of X
         // x <- x + sum of the np directions, taken into x
         auto direction = [&](int k) -> const T* {
             if constexpr (W0) return (sweep == 0 && !have_x && k == 0) ? reinterpret_cast<const T*>(w0) : pb + k * nodes;
@@ -1879,53 +1992,95 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
             for (int k = 0; k < np; ++k) y = fma4(alphas[k], ld4(direction(k) + k4), y);
             return y;
         };
-        bool first_it = true;   // p = z as stored
-        T beta = T(0);
-        while (rr > target) {
-            if (total >= a.max_iter) break;
-            const int ex = norm_exponent(rr) + 3;
-            const T sc = (T)ldexpf(1.0f, -ex);
-            T* pn = pb + (first_it ? 0 : np) * nodes;   // where p = z + beta p goes
-            T pq_acc = T(0);
+        // x <- x + the directions, which frees their buffers but for pc's
+        auto fold = [&]() {
 #pragma unroll 1
-            for (int k = 4 * tid; k < nodes; k += 4096) {   // four consecutive nodes of a row
-                const int g = k / NN, cc = k % NN;
-                const int kN = (g < NN - 1) ? k + NN : k, kS = (g > 0) ? k - NN : k;
-                T4 p4 = ld4(pc + k), pN = ld4(pc + kN), pS = ld4(pc + kS);
-                const T4 t4 = ld4(tv + k), tN = ld4(tv + kN), tS = ld4(tv + kS);
-                if (!first_it) {
-                    const T4 z4 = ld4(zv + k), zN = ld4(zv + kN), zS = ld4(zv + kS);
-                    p4 = fma4(beta, p4, z4);
-                    pN = fma4(beta, pN, zN);
-                    pS = fma4(beta, pS, zS);
-                }
-                const T t_[4] = {t4.x, t4.y, t4.z, t4.w};
-                const T pn_[4] = {pN.x, pN.y, pN.z, pN.w}, tn[4] = {tN.x, tN.y, tN.z, tN.w};
-                const T ps[4] = {pS.x, pS.y, pS.z, pS.w}, ts[4] = {tS.x, tS.y, tS.z, tS.w};
-                T p_[4] = {p4.x, p4.y, p4.z, p4.w};
-                T yc[4], q_[4];
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    if (!interior(g, cc + m)) p_[m] = T(0);
-                    yc[m] = t_[m] * p_[m];
-                }
-                // the nodes beyond the four, from the adjacent lanes: at a row's start the lane before
-                // ends in the padding column, which holds zero
-                const T yW0 = lane_before(yc[3]), yE3 = lane_after(yc[0]);
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const T yE = (m < 3) ? yc[m < 3 ? m + 1 : 3] : yE3;
-                    const T yW = (m > 0) ? yc[m > 0 ? m - 1 : 0] : yW0;
-                    const T yN = tn[m] * pn_[m];
-                    const T yS = (g > 0) ? ts[m] * ps[m] : T(0);
-                    q_[m] = interior(g, cc + m) ? p_[m] - t_[m] * ((yE + yW) + (yN + yS)) : T(0);
-                    pq_acc += p_[m] * q_[m];
-                }
-                if (!first_it) st4(pn + k, p_[0], p_[1], p_[2], p_[3]);
-                st4(qv + k, q_[0], q_[1], q_[2], q_[3]);
+            for (int k = 4 * tid; k < nodes; k += 4096) {
+                const T4 y = correction(k);
+                typename Vec4U<T>::type x4;
+                x4[0] = y.x; x4[1] = y.y; x4[2] = y.z; x4[3] = y.w;
+                *reinterpret_cast<typename Vec4U<T>::type*>(xv + k) = x4;
             }
-            const double pq = block_sum<NW>((double)pq_acc, red1);   // its barriers publish p and q
-            if (!first_it) pc = pn;
+            have_x = true;
+            np = 0;
+            __syncthreads();   // every thread has read the alphas and the first buffer
+        };
+        for (int it = 0; rr > target && total < a.max_iter; ++it) {
+            if (W0 && sweep == 0 && it == 0) {
+                if constexpr (W0) pc = reinterpret_cast<const T*>(w0);
+                rz = rw;
+                w_now = true;
+            } else {
+                if (np == NP) fold();
+                T* pn = pb + np * nodes;
+                const T* before = w_now ? nullptr : pc;   // w0 is no preconditioned residual: its beta follows
+                double rzn;
+                for (int staged = it > 0;; staged = 0) {
+                    rzn = dstg_direction<NN, T>(rv, pn, before, rz, Stab, staged, ex);
+                    ++napp;
+                    if (fabs(rzn) < INFINITY || !staged) break;
+                    ex = norm_exponent(rr) + 3;   // the residual outgrew the staged scale: redo from r
+                }
+                if (w_now) {   // conjugate to w0 by the definition
+                    double zq = 0.0;
+#pragma unroll 2
+                    for (int i = 0; i < RB; ++i) {
+                        const T4 z4 = ld4(pn + k0 + i * NN), q4 = ld4(qv + k0 + i * NN);
+                        zq += (double)(z4.x * q4.x + z4.y * q4.y) + (double)(z4.z * q4.z + z4.w * q4.w);
+                    }
+                    const T beta = (T)(-block_sum<NW>(zq, red2) / pq);
+#pragma unroll 2
+                    for (int i = 0; i < RB; ++i) {
+                        const T4 y = fma4(beta, ld4(pc + k0 + i * NN), ld4(pn + k0 + i * NN));
+                        st4(pn + k0 + i * NN, y.x, y.y, y.z, y.w);
+                    }
+                    __syncthreads();
+                    w_now = false;
+                }
+                rz = rzn;
+                pc = pn;
+            }
+            ex = norm_exponent(rr) + 3;
+            const T sc = (T)ldexpf(1.0f, -ex);
+            V4 q[QREG ? RB : 1];
+            T pq_acc = T(0);
+            {
+                uint32_t at = (uint32_t)(k0 * sizeof(T));
+                asm volatile("" : "+v"(at));   // else every row's addresses are kept in registers, and spill
+                const gcbp pB = uniform_base(pc), tB = uniform_base(tv), qB = uniform_base(qv);
+                V4 p4 = at_off<V4>(pB, at), t4 = at_off<V4>(tB, at);
+                V4 yS = {T(0), T(0), T(0), T(0)};   // t p of the row below
+                if (g0 > 0) yS = at_off<V4>(tB, at - ROW) * at_off<V4>(pB, at - ROW);
+                V4 yc = t4 * p4;
+#pragma unroll QU
+                for (int i = 0; i < RB; ++i) {
+                    const int g = g0 + i;   // past the last row its own again (unused)
+                    const uint32_t up = at + (g < NN - 1 ? ROW : 0);
+                    const V4 pN = at_off<V4>(pB, up), tN = at_off<V4>(tB, up);
+                    const V4 yN = tN * pN;
+                    // the nodes beyond the four, from the adjacent lanes: at a row's start the lane before
+                    // ends in the padding column, where every direction is zero
+                    const T yW0 = lane_before(yc[3]), yE3 = lane_after(yc[0]);
+                    V4 qi;
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        const T yE = (m < 3) ? yc[m < 3 ? m + 1 : 3] : yE3;
+                        const T yW = (m > 0) ? yc[m > 0 ? m - 1 : 0] : yW0;
+                        qi[m] = interior(g, cc + m) ? p4[m] - t4[m] * ((yE + yW) + (yN[m] + yS[m])) : T(0);
+                        pq_acc += p4[m] * qi[m];
+                    }
+                    p4 = pN;
+                    t4 = tN;
+                    yS = yc;
+                    yc = yN;
+                    // a row at a time: the compiler would load them all first, and spill
+                    asm volatile("" : "+v"(qi[0]), "+v"(qi[1]), "+v"(qi[2]), "+v"(qi[3]), "+v"(pq_acc)::"memory");
+                    if constexpr (QREG) q[i] = qi;
+                    else put_off<V4>(qB, at, qi);
+                    at += ROW;
+                }
+            }
+            pq = block_sum<NW>((double)pq_acc, red1);
             if (!(pq > 0.0) || !(pq < INFINITY)) {
                 broke = true;
                 break;
@@ -1933,56 +2088,31 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
             const T alpha = (T)(rz / pq);
             if (tid == 0) alphas[np] = alpha;
             T r_acc = T(0);
-#pragma unroll 4
-            for (int k = 4 * tid; k < nodes; k += 4096) {
-                T4 r4 = ld4(rv + k);
-                const T4 q4 = ld4(qv + k);
-                r4.x -= alpha * q4.x; r4.y -= alpha * q4.y; r4.z -= alpha * q4.z; r4.w -= alpha * q4.w;
-                r_acc += ((r4.x * r4.x + r4.y * r4.y) + (r4.z * r4.z + r4.w * r4.w));
-                st4(rv + k, r4.x, r4.y, r4.z, r4.w);
-                hf4 hb;
-                hb[0] = (_Float16)(float)(r4.x * sc); hb[1] = (_Float16)(float)(r4.y * sc);
-                hb[2] = (_Float16)(float)(r4.z * sc); hb[3] = (_Float16)(float)(r4.w * sc);
-                *reinterpret_cast<hf4*>(X + (k / NN) * (NN + 8) + (k % NN)) = hb;
+            {
+                uint32_t at = (uint32_t)(k0 * sizeof(T));
+                asm volatile("" : "+v"(at));
+                const gcbp rB = uniform_base(rv), qB = uniform_base(qv);
+                _Float16* xs = X + g0 * (NN + 8) + cc;
+#pragma unroll QU
+                for (int i = 0; i < RB; ++i) {
+                    V4 r4 = at_off<V4>(rB, at), q4;
+                    if constexpr (QREG) q4 = q[i];
+                    else q4 = at_off<V4>(qB, at);
+                    r4 -= alpha * q4;
+                    r_acc += ((r4[0] * r4[0] + r4[1] * r4[1]) + (r4[2] * r4[2] + r4[3] * r4[3]));
+                    put_off<V4>(rB, at, r4);
+                    if (QREG && w_now) put_off<V4>(qB, at, q4);
+                    hf4 hb;
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) hb[m] = (_Float16)(float)(r4[m] * sc);
+                    *reinterpret_cast<hf4*>(xs + i * (NN + 8)) = hb;
+                    at += ROW;
+                    if (i % 4 == 3) asm volatile("" ::: "memory");
+                }
             }
             rr = block_sum<NW>((double)r_acc, red2);   // its barrier also publishes X and alphas
             ++total;
             ++np;
-            first_it = false;
-            if (!(rr > target)) break;
-            double zacc = dstg_precondition<NN, T>(rv, zv, Stab, lamtab, 1, ex, 1);
-            ++napp;
-            double rzn = block_sum<NW>(zacc, red1);
-            if (!(fabs(rzn) < INFINITY)) {   // the residual outgrew the staged scale: redo from r
-                __syncthreads();
-                zacc = dstg_precondition<NN, T>(rv, zv, Stab, lamtab, 0, norm_exponent(rr) + 3, 1);
-                rzn = block_sum<NW>(zacc, red2);
-                ++napp;
-            }
-            beta = (T)(rzn / rz);
-            if (w_first) {   // conjugate to w0 by the definition (it was no preconditioned residual)
-                double zq = 0.0;
-#pragma unroll 2
-                for (int k = 4 * tid; k < nodes; k += 4096) {
-                    const T4 z4 = ld4(zv + k), q4 = ld4(qv + k);
-                    zq += (double)(z4.x * q4.x + z4.y * q4.y) + (double)(z4.z * q4.z + z4.w * q4.w);
-                }
-                beta = (T)(-block_sum<NW>(zq, red2) / pq);
-                w_first = false;
-            }
-            rz = rzn;
-            if (np == NP) {   // no buffer left: fold the directions into x (the last one stays readable)
-#pragma unroll 1
-                for (int k = 4 * tid; k < nodes; k += 4096) {
-                    const T4 y = correction(k);
-                    typename Vec4U<T>::type x4;
-                    x4[0] = y.x; x4[1] = y.y; x4[2] = y.z; x4[3] = y.w;
-                    *reinterpret_cast<typename Vec4U<T>::type*>(xv + k) = x4;
-                }
-                have_x = true;
-                np = 0;
-                __syncthreads();   // every thread has read the alphas and the first buffer
-            }
         }
         // refinement: dx = D^{-1/2} y in T (over q), its observed nodes, then the FP64 residual
         __syncthreads();
