@@ -67,7 +67,7 @@ struct DstShape {
     static constexpr int NSG = NB / SP;       // strip groups
     static constexpr int TPW = NB * NB / (NW * SP);   // output tiles per wave and strip
     static constexpr int LD = NN + 8;         // 16-bit row stride (16-byte aligned, spreads banks)
-    static constexpr int LDZ = NN + 4;        // fp32 row stride of the result
+    static constexpr int LDZ = NN + 4;        // fp32 row (column) stride of the result
     // LDS: Z with R^T and T2^T (dead when Z is written) in its first part, then T1 and T3
     static constexpr int B_AT = NN * LDZ * 4, BYTES = B_AT + NN * LD * 2;
     static_assert(NN * LD * 2 <= B_AT, "the first buffer lies inside Z");
@@ -101,13 +101,16 @@ __device__ __forceinline__ void dst_stage_lam(float* lam, const float* __restric
     for (int k = threadIdx.x; k < NN; k += 64 * NW) lam[k] = lamtab[k];
 }
 
-// z = L^{-1} r into Z[g][c] in LDS (at smem), from the thread's strip of r.  Bound by LDS: at 128^2 the
+// z = L^{-1} r into Z[g][c] (COLS: Z[c][g]) in LDS (at smem), from the thread's strip of r.  Bound by LDS: at 128^2 the
 // four products read 512 KB of operand fragments and the passes between them move another 250 KB
 // (about 6100 clocks at 128 bytes per clock).  So each wave asks for the next tile's fragments before
 // it multiplies this one's (with one tile at a time, every fragment's LDS round trip stood between
 // two products), the eigenvalues come from LDS (from memory they cost a wait per tile of the second
-// product), and the strips of S stay in registers between applications.
-template <typename T, int NN, int R, int NW>
+// product), and the strips of S stay in registers between applications.  By columns a thread reads its
+// strip of the result 16 bytes at a time (4096 potentials at 128^2 1.86 -> 1.83 ms, a stage of 1024 at 64^2 in FP64
+// 2.5% less); the kernels that keep the solution have no four registers in a row to spare for that, and
+// spill (the two solves of 2048 gradients at 128^2 2.64 -> 3.04 ms).
+template <typename T, int NN, int R, int NW, bool COLS>
 __device__ __forceinline__ void dst_apply(const T (&rin)[R], double rr, unsigned char* smem, const float* lamt,
                                           const DstStrips<NN, NW>& S, int c, int b, int wave, int lane) {
     using DS = DstShape<NN, NW>;
@@ -123,7 +126,7 @@ __device__ __forceinline__ void dst_apply(const T (&rin)[R], double rr, unsigned
     const float sc = ldexpf(1.0f, -ex), unsc = ldexpf(1.0f, ex);
     _Float16* bufA = reinterpret_cast<_Float16*>(smem);                // R^T, later T2^T
     _Float16* bufB = reinterpret_cast<_Float16*>(smem + DS::B_AT);     // T1, later T3
-    float* Z = reinterpret_cast<float*>(smem);   // Z[g][c]: lanes of a row read consecutive words
+    float* Z = reinterpret_cast<float*>(smem);   // Z[g][c]: lanes of a row read consecutive words; or Z[c][g]
     const int lr = lane & 15, lk = lane >> 4;
     const int sg = wave % NSG, t0 = (wave / NSG) * TPW;   // the wave's strips of S and its first data tile
     {   // stage R^T[c][g] = fp16(r 2^-e): the thread's strip is contiguous
@@ -195,9 +198,10 @@ __device__ __forceinline__ void dst_apply(const T (&rin)[R], double rr, unsigned
     // T3[g][l] = sum_k S[g][k] T2[k][l], as (T2^T S)[l][g]
     product(bufA, std::false_type{}, put(bufB));
     __syncthreads();
-    // Z[g][c] = sum_l T3[g][l] S[l][c], as (S T3^T)[c][g]
-    product(bufB, std::true_type{}, [&](int tile, int q, f4 acc) __attribute__((always_inline)) {
-        *reinterpret_cast<float4*>(Z + (tile * 16 + lr) * LDZ + (sg * SP + q) * 16 + 4 * lk) =
+    // Z[g][c] = sum_l T3[g][l] S[l][c], for rows as (S T3^T)[c][g]
+    product(bufB, std::integral_constant<bool, !COLS>{}, [&](int tile, int q, f4 acc) __attribute__((always_inline)) {
+        const int strip = (sg * SP + q) * 16;
+        *reinterpret_cast<float4*>(Z + (COLS ? (strip + lr) * LDZ + tile * 16 : (tile * 16 + lr) * LDZ + strip) + 4 * lk) =
             make_float4(acc[0] * unsc, acc[1] * unsc, acc[2] * unsc, acc[3] * unsc);
     });
     __syncthreads();
@@ -226,7 +230,7 @@ __global__ __launch_bounds__(NN * NN / R) void dst_apply_kernel(const float* __r
     float* lamt = reinterpret_cast<float*>(smem + DstShape<NN, NW>::BYTES);
     dst_stage_lam<NN, NW>(lamt, lamtab);
     const double rr = block_sum<NW>(acc, red);
-    dst_apply<float, NN, R, NW>(r, rr, smem, lamt, S, c, b, tid >> 6, tid & 63);
+    dst_apply<float, NN, R, NW, false>(r, rr, smem, lamt, S, c, b, tid >> 6, tid & 63);
     const float* Z = reinterpret_cast<const float*>(smem);
 #pragma unroll
     for (int k = 0; k < R; ++k) zout[base + (b * R + k) * NN + c] = Z[(b * R + k) * DstShape<NN, NW>::LDZ + c];
@@ -871,16 +875,27 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
     int napp = 0;   // preconditioner applications (same in every thread)
     auto precondition = [&](const T (&rin)[R], double rrin) __attribute__((always_inline)) {
         if constexpr (DST) {
-            dst_apply<T, NN, R, NW>(rin, rrin, smem, lamt, strips, c, b, wave, lane);
+            dst_apply<T, NN, R, NW, !KEEP>(rin, rrin, smem, lamt, strips, c, b, wave, lane);
             ++napp;
         }
     };
-    auto zval = [&](int r) __attribute__((always_inline)) -> T {
+    auto zvals = [&](T (&z)[R]) __attribute__((always_inline)) {
         if constexpr (DST) {
             const float* Z = reinterpret_cast<const float*>(smem);
-            return (T)Z[(b * R + r) * DS::LDZ + c];
-        } else {
-            return T(0);
+            static_assert(R % 4 == 0, "16-byte reads");
+#pragma unroll
+            for (int r = 0; r < R; r += 4) {
+                if constexpr (!KEEP) {
+                    const float4 v = *reinterpret_cast<const float4*>(Z + c * DS::LDZ + b * R + r);
+                    z[r] = (T)v.x;
+                    z[r + 1] = (T)v.y;
+                    z[r + 2] = (T)v.z;
+                    z[r + 3] = (T)v.w;
+                } else {
+#pragma unroll
+                    for (int k = r; k < r + 4; ++k) z[k] = (T)Z[(b * R + k) * DS::LDZ + c];
+                }
+            }
         }
     };
     // observations of the forward solution: G, Phi, and the adjoint's sources (G - y) / sigma^2
@@ -1032,8 +1047,7 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
                 if (!w_first) {
                     __syncthreads();              // the transform buffers alias the staging slots
                     precondition(rv, rr);
-#pragma unroll
-                    for (int r = 0; r < R; ++r) p[r] = zval(r);
+                    zvals(p);
                 }
                 double zacc = 0.0;
 #pragma unroll
@@ -1102,12 +1116,10 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
                 if constexpr (DST) {
                     precondition(rv, rr);
                     T z[R];
+                    zvals(z);
                     T rz_acc = T(0);
 #pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        z[r] = zval(r);
-                        rz_acc += rv[r] * z[r];
-                    }
+                    for (int r = 0; r < R; ++r) rz_acc += rv[r] * z[r];
                     const double rzn = block_sum<NW>((double)rz_acc, red1);
                     T beta = (T)(rzn / rz);
                     if (w_first) {   // p was no preconditioned residual: conjugate to it by the definition
