@@ -361,11 +361,10 @@ __device__ __noinline__ double strip_residual(const double* __restrict__ e_, con
     static_assert(NN % 64 == 0, "a wave covers consecutive columns of one row");
     constexpr int NP1 = NN + 1;
     const double inv_h2 = (double)NN * (double)NN;
-    gcdp e = (gcdp)e_;
-    gcdp xo = (gcdp)xo_;
-    gcp<SD> sd = (gcp<SD>)sd_;
+    const gcbp e = uniform_base(e_), xo = uniform_base(xo_), sd = uniform_base(sd_);
     __attribute__((address_space(3))) T* tb = (__attribute__((address_space(3))) T*)tb_;
     const int i = c + 1;
+    const uint32_t own = (uint32_t)(g0 * NN + c), eown = (uint32_t)((g0 + 1) * NP1 + i) * 8u;
     const bool colin = c < NN - 1;
     double acc = 0.0;
     // SRC: the sources in this thread's strip (column c, rows g0 .. g0 + R - 1), found once; a strip
@@ -416,7 +415,7 @@ __device__ __noinline__ double strip_residual(const double* __restrict__ e_, con
             const int g = g0 + r;
             const bool in = colin && g < NN - 1;
             const double fr = rhs_at(r);
-            const double sdv = (double)sd[g * NN + c];
+            const double sdv = (double)at_off<SD>(sd, (own + r * NN) * (uint32_t)sizeof(SD));
             acc += in ? fr * fr : 0.0;
             tb[NN + 1 + r * NN] = in ? (T)(sdv * fr) : T(0);
         }
@@ -429,8 +428,8 @@ __device__ __noinline__ double strip_residual(const double* __restrict__ e_, con
     const bool xEok = c0 + 64 < NN - 1, xWok = c0 > 0;
     kcdp eu = (kcdp)wave_uniform(e_);
     const int g0u = __builtin_amdgcn_readfirstlane(g0);
-    double eS = e[g0 * NP1 + i], eC = e[(g0 + 1) * NP1 + i];
-    double xS = xo[max(g0 - 1, 0) * NN + c], xC = xo[g0 * NN + c];
+    double eS = at_off<double>(e, eown - NP1 * 8u), eC = at_off<double>(e, eown);
+    double xS = at_off<double>(xo, (own - (g0 > 0 ? NN : 0)) * 8u), xC = at_off<double>(xo, own * 8u);
     xS = (g0 > 0 && colin) ? xS : 0.0;
     xC = (g0 < NN - 1 && colin) ? xC : 0.0;
     constexpr int B = R < 8 ? R : 8;   // rows whose loads are issued together
@@ -438,17 +437,20 @@ __device__ __noinline__ double strip_residual(const double* __restrict__ e_, con
 #pragma unroll 1
     for (int r0 = 0; r0 < R; r0 += B) {
         double eN[B], xN[B], sdv[B], eEe[B], eWe[B], xEe[B], xWe[B];
+        const uint32_t at = own + (uint32_t)(r0 * NN), eat = eown + (uint32_t)(r0 * NP1) * 8u;
+        const uint32_t xE = (uint32_t)((g0 + r0) * NN + cxE) * 8u, xW = (uint32_t)((g0 + r0) * NN + cxW) * 8u;
 #pragma unroll
         for (int k = 0; k < B; ++k) {
-            const int g = g0 + r0 + k, j = g + 1;
-            eN[k] = e[min(j + 1, NN) * NP1 + i];
-            xN[k] = xo[min(g + 1, NN - 1) * NN + c];
-            sdv[k] = (double)sd[g * NN + c];
+            // the row above; only a strip's last row can be the grid's, and reads its own (unused)
+            const bool top = k + 1 == B && g0 + r0 + B == NN;
+            eN[k] = at_off<double>(e, eat + k * NP1 * 8u + (top ? 0u : NP1 * 8u));
+            xN[k] = at_off<double>(xo, (at + k * NN + (top ? 0 : NN)) * 8u);
+            sdv[k] = (double)at_off<SD>(sd, (at + k * NN) * (uint32_t)sizeof(SD));
             const int ju = g0u + r0 + k + 1;
-            eEe[k] = SE ? eu[ju * NP1 + ieE] : e[ju * NP1 + ieE];
-            eWe[k] = SE ? eu[ju * NP1 + ieW] : e[ju * NP1 + ieW];
-            xEe[k] = xo[g * NN + cxE];
-            xWe[k] = xo[g * NN + cxW];
+            eEe[k] = SE ? eu[ju * NP1 + ieE] : at_off<double>(e, (uint32_t)(ju * NP1 + ieE) * 8u);
+            eWe[k] = SE ? eu[ju * NP1 + ieW] : at_off<double>(e, (uint32_t)(ju * NP1 + ieW) * 8u);
+            xEe[k] = at_off<double>(xo, xE + k * NN * 8u);
+            xWe[k] = at_off<double>(xo, xW + k * NN * 8u);
         }
 #pragma unroll
         for (int k = 0; k < B; ++k) {
@@ -477,24 +479,22 @@ __device__ __noinline__ double strip_residual(const double* __restrict__ e_, con
 // x += D^{-1/2} y for the strip, y staged in its LDS slots (x = D^{-1/2} y when `first`).
 template <typename T, int NN, int R, typename SD>
 __device__ __noinline__ void strip_update(double* xo_, const SD* sd_, const T* tb_, int c, int g0, bool first) {
-    gdp xo = (gdp)xo_;
-    gcp<SD> sd = (gcp<SD>)sd_;
+    const gcbp xo = uniform_base(xo_), sd = uniform_base(sd_);
+    const uint32_t own = (uint32_t)(g0 * NN + c);
     const __attribute__((address_space(3))) T* tb = (const __attribute__((address_space(3))) T*)tb_;
     constexpr int B = R < 16 ? R : 16;   // rows whose loads are issued together
 #pragma unroll 1
     for (int r0 = 0; r0 < R; r0 += B) {
         double sdv[B], xv[B];
+        const uint32_t at = own + (uint32_t)(r0 * NN);
 #pragma unroll
         for (int k = 0; k < B; ++k) {
-            const int g = g0 + r0 + k;
-            sdv[k] = (double)sd[g * NN + c];
-            xv[k] = first ? 0.0 : xo[g * NN + c];
+            sdv[k] = (double)at_off<SD>(sd, (at + k * NN) * (uint32_t)sizeof(SD));
+            xv[k] = first ? 0.0 : at_off<double>(xo, (at + k * NN) * 8u);
         }
 #pragma unroll
-        for (int k = 0; k < B; ++k) {
-            const int g = g0 + r0 + k;
-            xo[g * NN + c] = xv[k] + sdv[k] * (double)tb[NN + 1 + (r0 + k) * NN];
-        }
+        for (int k = 0; k < B; ++k)
+            put_off<double>(xo, (at + k * NN) * 8u, xv[k] + sdv[k] * (double)tb[NN + 1 + (r0 + k) * NN]);
     }
 }
 
