@@ -598,6 +598,118 @@ __device__ __forceinline__ double strip_refine(const double* __restrict__ e_, do
     return acc;
 }
 
+// The same step at 128^2 with the nodes dealt out anew: a thread takes two columns of a band of rows, a wave
+// whole rows.  The strips' way costs some 50 instructions a node, which with two waves per SIMD is
+// what a step takes; in pairs the loads and stores are twice as wide, half of the horizontal neighbours are the thread's
+// own, a row's address and its place in the grid are scalars, and D^{-1/2} is read once.  NT threads.
+// The inner solution y is in the LDS slots of its strips.  Four rows at a time (two 1.73, eight spill: 1.79 ms) and
+// without loads ahead of a block (they spill: 1.88).  4096 potentials 1.82 -> 1.71 ms, of 8 particles 105 -> 95 us.
+template <typename T, int NN, int NT, typename SD, bool SE>
+__device__ __noinline__ double pair_refine(const double* __restrict__ e_, double* __restrict__ rb_,
+                                           const SD* __restrict__ sd_, T* ly_, T* out_, bool first, double f,
+                                           int n_obs) {
+    static_assert(NN == 128, "a row is 64 pairs");
+    constexpr int NP1 = NN + 1, PAD = NN + 1, RB = NN * NN / 2 / NT, B = RB < 4 ? RB : 4;
+    typedef T T2 __attribute__((ext_vector_type(2)));
+    typedef SD SD2 __attribute__((ext_vector_type(2)));
+    typedef double D2 __attribute__((ext_vector_type(2)));
+    typedef double D2U __attribute__((ext_vector_type(2), aligned(8)));   // rows of e start on any double
+    typedef __attribute__((address_space(3))) T* ltp;
+    typedef __attribute__((address_space(3))) T2* ltp2;
+    const double n2 = (double)NN * (double)NN;
+    const int tid = threadIdx.x, lane = tid & 63, g0 = __builtin_amdgcn_readfirstlane(tid >> 6) * RB, c = 2 * lane;
+    const gcbp e = uniform_base(e_) + (g0 + 1) * NP1 * 8, rb = uniform_base(rb_) + g0 * NN * 8,
+               sd = uniform_base(sd_) + g0 * NN * (int)sizeof(SD);
+    const uint32_t eo = (uint32_t)(c + 1) * 8u, ro_ = (uint32_t)c * 8u;
+    kcdp eu = (kcdp)wave_uniform(e_) + (g0 + 1) * NP1;
+    ltp ly = (ltp)ly_;
+    ltp y = ly + PAD + g0 * NN + c;
+    ltp2 out = (ltp2)((ltp)out_ + g0 * NN + c);
+    SD2 sv[RB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) sv[r] = at_off<SD2>(sd + r * NN * (int)sizeof(SD), (uint32_t)c * (uint32_t)sizeof(SD));
+    D2U eN[B];
+    D2 ro[B];
+    double eW0[B];
+    auto load = [&](int blk) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const int r = blk * B + k;
+            const int up = g0 + r < NN - 1 ? r + 1 : r;   // past the last row its own (unused)
+            eN[k] = at_off<D2U>(e + up * NP1 * 8, eo);
+            eW0[k] = SE ? eu[r * NP1] : at_off<double>(e + r * NP1 * 8, 0u);
+            ro[k] = D2{f, f};
+        }
+        if (!first) {
+#pragma unroll
+            for (int k = 0; k < B; ++k) ro[k] = at_off<D2>(rb + (blk * B + k) * NN * 8, ro_);
+        }
+    };
+    D2U eS = at_off<D2U>(e - NP1 * 8, eo), eC = at_off<D2U>(e, eo);
+    __syncthreads();   // y is whole
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+        y[r * NN] = (T)sv[r][0] * y[r * NN];
+        y[r * NN + 1] = (T)sv[r][1] * y[r * NN + 1];
+        if (r % 4 == 3) asm volatile("" ::: "memory");
+    }
+    for (int k = tid; k < PAD; k += NT) {   // rows -1 and NN, and column -1, of the exchange array
+        ly[k] = T(0);
+        ly[PAD + NN * NN + k] = T(0);
+    }
+    __syncthreads();
+    if (tid < n_obs) {
+        const int at = g_src_at[tid];
+        if (at >= 0) g_src_w[tid] += (double)ly[PAD + at];
+    }
+    double dS0 = (double)y[-NN], dS1 = (double)y[1 - NN], d0 = (double)y[0], d1 = (double)y[1];
+    double acc = 0.0;
+#pragma unroll
+    for (int blk = 0; blk < RB / B; ++blk) {
+        load(blk);
+        T xW[B], xE[B], x0[B], x1[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const int r = blk * B + k;
+            xW[k] = y[r * NN - 1];
+            xE[k] = y[r * NN + 2];
+            x0[k] = y[(r + 1) * NN];
+            x1[k] = y[(r + 1) * NN + 1];
+        }
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const int r = blk * B + k;
+            const D2U en = eN[k];
+            const double eW = from_prev_lane(eC[1], eW0[k]), eE = from_next_lane(eC[0], 0.0);
+            const double dW = (double)xW[k], dE = (double)xE[k], dN0 = (double)x0[k], dN1 = (double)x1[k];
+            const double flux0 = eC[1] * (d0 - d1) + eW * (d0 - dW) + en[0] * (d0 - dN0) + eS[0] * (d0 - dS0);
+            const double flux1 = eE * (d1 - dE) + eC[0] * (d1 - d0) + en[1] * (d1 - dN1) + eS[1] * (d1 - dS1);
+            D2 res;
+            res[0] = ro[k][0] - eC[0] * n2 * flux0;
+            res[1] = ro[k][1] - eC[1] * n2 * flux1;
+            const bool row = g0 + r < NN - 1;   // uniform
+            res[0] = row ? res[0] : 0.0;
+            res[1] = row && lane < 63 ? res[1] : 0.0;
+            acc += res[0] * res[0];
+            acc += res[1] * res[1];
+            asm volatile("" : "+v"(acc), "+v"(res)::"memory");   // a row at a time: the compiler would hold many, and spill
+            put_off<D2>(rb + r * NN * 8, ro_, res);
+            T2 o;
+            o[0] = (T)((double)sv[r][0] * res[0]);
+            o[1] = (T)((double)sv[r][1] * res[1]);
+            out[r * (NN / 2)] = o;
+            eS = eC;
+            eC = en;
+            dS0 = d0;
+            dS1 = d1;
+            d0 = dN0;
+            d1 = dN1;
+        }
+        asm volatile("" ::: "memory");   // a block at a time: loads further ahead spill
+    }
+    return acc;
+}
+
 // The first scaled residual D^{-1/2} f into the strip's `out` slots.
 template <typename T, int NN, int R, typename SD>
 __device__ __forceinline__ void strip_first(const SD* __restrict__ sd_, T* out_, int c, int g0, double f) {
@@ -1147,7 +1259,9 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
 #pragma unroll
             for (int r = 0; r < R; ++r) tb[NN + 1 + r * NN] = x[r];
             if constexpr (!KEEP) {
-                if constexpr (WIDE)
+                if constexpr (NN == 128)
+                    acc = pair_refine<T, NN, NT, SD, SE>(e, xo, sd, ly, lout, sweep == 0, a.f, a.n_obs);
+                else if constexpr (WIDE)
                     acc = strip_refine_call<T, NN, R, SD, SE>(e, xo, sd, ly, lout, c, b * R, sweep == 0, a.f, a.n_obs);
                 else
                     acc = strip_refine<T, NN, R, SD, SE>(e, xo, sd, ly, lout, c, b * R, sweep == 0, a.f, a.n_obs);
