@@ -116,3 +116,35 @@ def test_gather_widths(N, K, off):
     keep = np.arange(N) != N // 2
     assert torch.equal(xo, want) and (dst[:off] == 3.0).all() and (dst[off + N * K:] == 3.0).all()
     assert np.array_equal(po.cpu().numpy()[keep], phi.cpu().numpy()[ii][keep])
+
+
+def test_many_workgroups_in_a_graph():
+    """The launch chains captured once and replayed on new potentials, eager calls in between: the same bits."""
+    from paper_2503_16028_amd import smc
+    banner("temper and resample chains in a graph")
+    N = 20011
+    phi, W = t(inputs.potentials(N, 1)), torch.empty(N, dtype=torch.float64, device=DEV)
+    idx = torch.empty(N, dtype=torch.int32, device=DEV)
+    tau = t([0.0])
+    h, tau_new, lz = (torch.empty(1, dtype=torch.float64, device=DEV) for _ in range(3))
+    u = inputs.u53(5)
+
+    def both(W, idx, h, tau_new, lz):
+        smc.smc_temper(N, phi, tau, 0.5, h, tau_new, W, lz)
+        smc.smc_resample(N, W, u, idx)
+
+    both(W, idx, h, tau_new, lz)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        both(W, idx, h, tau_new, lz)
+    for r in range(3):
+        phi.copy_(t(inputs.potentials(N, 10 + r)))
+        tau.fill_(0.1 * r)
+        g.replay()
+        torch.cuda.synchronize()
+        e = [torch.empty_like(a) for a in (W, idx, h, tau_new, lz)]
+        both(*e)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(e, (W, idx, h, tau_new, lz))), r
+        assert not torch.equal(idx, torch.arange(N, dtype=torch.int32, device=DEV))
