@@ -873,6 +873,63 @@ __device__ __forceinline__ void strip_setup(const double* __restrict__ e_, SD* _
     }
 }
 
+// The same at 128^2 by pairs of columns, as pair_refine deals the nodes out (t into the strips' slots: read them
+// after a barrier); FIRST: with the first scaled residual D^{-1/2} f into `out`, which saves strip_first its
+// pass.  4096 potentials 1.72 -> 1.61 ms, of 8 particles 95 -> 90 us.
+template <typename T, int NN, int NT, typename SD, bool SE, bool FIRST>
+__device__ __noinline__ void pair_setup(const double* __restrict__ e_, SD* __restrict__ sd_, T* ly_, T* out_, double f) {
+    static_assert(NN == 128, "a row is 64 pairs");
+    constexpr int NP1 = NN + 1, PAD = NN + 1, RB = NN * NN / 2 / NT, B = RB < 8 ? RB : 8;
+    typedef T T2 __attribute__((ext_vector_type(2)));
+    typedef SD SD2 __attribute__((ext_vector_type(2)));
+    typedef double D2U __attribute__((ext_vector_type(2), aligned(8)));
+    typedef __attribute__((address_space(3))) T* ltp;
+    typedef __attribute__((address_space(3))) T2* ltp2;
+    const double h = 1.0 / NN;
+    const int lane = threadIdx.x & 63, g0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * RB, c = 2 * lane;
+    const gcbp e = uniform_base(e_) + (g0 + 1) * NP1 * 8, sd = uniform_base(sd_) + g0 * NN * (int)sizeof(SD);
+    const uint32_t eo = (uint32_t)(c + 1) * 8u;
+    kcdp eu = (kcdp)wave_uniform(e_) + (g0 + 1) * NP1;
+    ltp y = (ltp)ly_ + PAD + g0 * NN + c;
+    ltp2 out = (ltp2)((ltp)out_ + g0 * NN + c);
+    D2U eS = at_off<D2U>(e - NP1 * 8, eo), eC = at_off<D2U>(e, eo);
+#pragma unroll
+    for (int r0 = 0; r0 < RB; r0 += B) {
+        D2U eN[B];
+        double eW0[B];
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const int r = r0 + k, up = g0 + r < NN - 1 ? r + 1 : r;   // past the last row its own (unused)
+            eN[k] = at_off<D2U>(e + up * NP1 * 8, eo);
+            eW0[k] = SE ? eu[r * NP1] : at_off<double>(e + r * NP1 * 8, 0u);
+        }
+#pragma unroll
+        for (int k = 0; k < B; ++k) {
+            const int r = r0 + k;
+            const bool row = g0 + r < NN - 1;   // uniform
+            const double S0 = eC[1] + from_prev_lane(eC[1], eW0[k]) + eN[k][0] + eS[0];
+            const double S1 = from_next_lane(eC[0], 0.0) + eC[0] + eN[k][1] + eS[1];
+            const double rs0 = rsqrt64(eC[0] * S0), rs1 = rsqrt64(eC[1] * S1);
+            const bool in0 = row, in1 = row && lane < 63;
+            SD2 sv;
+            sv[0] = in0 ? (SD)(h * rs0) : SD(1);
+            sv[1] = in1 ? (SD)(h * rs1) : SD(1);
+            put_off<SD2>(sd + r * NN * (int)sizeof(SD), (uint32_t)c * (uint32_t)sizeof(SD), sv);
+            y[r * NN] = in0 ? (T)(eC[0] * rs0) : T(0);
+            y[r * NN + 1] = in1 ? (T)(eC[1] * rs1) : T(0);
+            if constexpr (FIRST) {
+                T2 o;
+                o[0] = in0 ? (T)((double)sv[0] * f) : T(0);
+                o[1] = in1 ? (T)((double)sv[1] * f) : T(0);
+                out[r * (NN / 2)] = o;
+            }
+            eS = eC;
+            eC = eN[k];
+            asm volatile("" ::: "memory");
+        }
+    }
+}
+
 // The same out of line.  A wide strip's pass unrolls over many rows and would take its registers from
 // the conjugate-gradient loop; a narrow one (eight rows and fewer) is small, and inline the kernel's own
 // register limit holds for it too (out of line it took 132 registers at 64^2: one workgroup per
@@ -948,7 +1005,10 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
     }
     // ---- setup: D^{-1/2} (workspace, in SD) and t (registers), staged through the thread's own LDS slots
     if constexpr (SPLIT) {
-        if constexpr (WIDE) strip_setup_call<T, NN, R, SD, SE>(e, sd, tb, c, b * R);
+        if constexpr (NN == 128) {
+            pair_setup<T, NN, NT, SD, SE, !KEEP>(e, sd, ly, lout, a.f);
+            __syncthreads();   // t is whole
+        } else if constexpr (WIDE) strip_setup_call<T, NN, R, SD, SE>(e, sd, tb, c, b * R);
         else strip_setup<T, NN, R, SD, SE>(e, sd, tb, c, b * R);
     } else {
         // column i of e, rows j-1, j, j+1 carried along the strip (j = g + 1)
@@ -1068,7 +1128,8 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
             if constexpr (!KEEP) {   // the residual: f at first, then as the last step left it
                 if (sweep == 0) {
                     rr64 = a.f * a.f * (double)((NN - 1) * (NN - 1));
-                    if constexpr (WIDE) strip_first_call<T, NN, R, SD>(sd, lout, c, b * R, a.f);
+                    if constexpr (NN == 128) {}   // the setup left it
+                    else if constexpr (WIDE) strip_first_call<T, NN, R, SD>(sd, lout, c, b * R, a.f);
                     else strip_first<T, NN, R, SD>(sd, lout, c, b * R, a.f);
                 }
             } else if constexpr (SPLIT) {
