@@ -827,8 +827,7 @@ __device__ __noinline__ double pair_residual(const double* __restrict__ e_, cons
     static_assert(NN == 128, "a row is 64 pairs");
     constexpr int NP1 = NN + 1, PAD = NN + 1, RB = NN * NN / 2 / NT, B = RB < 4 ? RB : 4;
     typedef SD SD2 __attribute__((ext_vector_type(2)));
-    typedef double D2 __attribute__((ext_vector_type(2)));
-    typedef double D2U __attribute__((ext_vector_type(2), aligned(8)));
+    typedef double D2U __attribute__((ext_vector_type(2), aligned(8)));   // x may be a caller's, on any double
     typedef __attribute__((address_space(3))) T* ltp;
     const double inv_h2 = (double)NN * (double)NN;
     const int lane = threadIdx.x & 63, g0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * RB, c = 2 * lane;
@@ -839,7 +838,7 @@ __device__ __noinline__ double pair_residual(const double* __restrict__ e_, cons
     ltp y = (ltp)ly_ + PAD + g0 * NN + c;
     const bool last = lane == 63;   // its second column is the padding
     D2U eS = at_off<D2U>(e - NP1 * 8, eo), eC = at_off<D2U>(e, eo);
-    D2 xS = at_off<D2>(xo - (g0 > 0 ? NN * 8 : 0), xoff), xC = at_off<D2>(xo, xoff);
+    D2U xS = at_off<D2U>(xo - (g0 > 0 ? NN * 8 : 0), xoff), xC = at_off<D2U>(xo, xoff);
     xS[0] = g0 > 0 ? xS[0] : 0.0;
     xS[1] = g0 > 0 && !last ? xS[1] : 0.0;
     xC[1] = last ? 0.0 : xC[1];
@@ -847,14 +846,14 @@ __device__ __noinline__ double pair_residual(const double* __restrict__ e_, cons
 #pragma unroll
     for (int r0 = 0; r0 < RB; r0 += B) {
         D2U eN[B];
-        D2 xN[B];
+        D2U xN[B];
         SD2 sv[B];
         double eW0[B];
 #pragma unroll
         for (int k = 0; k < B; ++k) {
             const int r = r0 + k, up = g0 + r < NN - 1 ? r + 1 : r;   // past the last row its own (unused)
             eN[k] = at_off<D2U>(e + up * NP1 * 8, eo);
-            xN[k] = at_off<D2>(xo + up * NN * 8, xoff);
+            xN[k] = at_off<D2U>(xo + up * NN * 8, xoff);
             sv[k] = at_off<SD2>(sd + r * NN * (int)sizeof(SD), (uint32_t)c * (uint32_t)sizeof(SD));
             eW0[k] = SE ? eu[r * NP1] : at_off<double>(e + r * NP1 * 8, 0u);
         }
@@ -864,7 +863,7 @@ __device__ __noinline__ double pair_residual(const double* __restrict__ e_, cons
             const bool row = g0 + r < NN - 1, above = g0 + r + 1 < NN - 1;   // uniform
             const double eW = from_prev_lane(eC[1], eW0[k]), eE = from_next_lane(eC[0], 0.0);
             const double xw = from_prev_lane(xC[1], 0.0), xe = from_next_lane(xC[0], 0.0);
-            D2 xn;
+            D2U xn;
             xn[0] = above ? xN[k][0] : 0.0;
             xn[1] = above && !last ? xN[k][1] : 0.0;
             const double flux0 = eC[1] * (xC[0] - xC[1]) + eW * (xC[0] - xw) + eN[k][0] * (xC[0] - xn[0]) + eS[0] * (xC[0] - xS[0]);
@@ -890,7 +889,7 @@ __device__ __noinline__ void pair_update(double* xo_, const SD* sd_, const T* ly
     static_assert(NN == 128, "a row is 64 pairs");
     constexpr int PAD = NN + 1, RB = NN * NN / 2 / NT, B = RB < 8 ? RB : 8;
     typedef SD SD2 __attribute__((ext_vector_type(2)));
-    typedef double D2 __attribute__((ext_vector_type(2)));
+    typedef double D2U __attribute__((ext_vector_type(2), aligned(8)));   // x may be a caller's, on any double
     const int lane = threadIdx.x & 63, g0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * RB, c = 2 * lane;
     const gcbp xo = uniform_base(xo_) + g0 * NN * 8, sd = uniform_base(sd_) + g0 * NN * (int)sizeof(SD);
     const uint32_t xoff = (uint32_t)c * 8u;
@@ -898,19 +897,19 @@ __device__ __noinline__ void pair_update(double* xo_, const SD* sd_, const T* ly
 #pragma unroll
     for (int r0 = 0; r0 < RB; r0 += B) {
         SD2 sv[B];
-        D2 xv[B];
+        D2U xv[B];
 #pragma unroll
         for (int k = 0; k < B; ++k) {
             sv[k] = at_off<SD2>(sd + (r0 + k) * NN * (int)sizeof(SD), (uint32_t)c * (uint32_t)sizeof(SD));
-            xv[k] = first ? D2{0.0, 0.0} : at_off<D2>(xo + (r0 + k) * NN * 8, xoff);
+            xv[k] = first ? D2U{0.0, 0.0} : at_off<D2U>(xo + (r0 + k) * NN * 8, xoff);
         }
 #pragma unroll
         for (int k = 0; k < B; ++k) {
             const int r = r0 + k;
-            D2 x;
+            D2U x;
             x[0] = xv[k][0] + (double)sv[k][0] * (double)y[r * NN];
             x[1] = xv[k][1] + (double)sv[k][1] * (double)y[r * NN + 1];
-            put_off<D2>(xo + r * NN * 8, xoff, x);
+            put_off<D2U>(xo + r * NN * 8, xoff, x);
         }
         asm volatile("" ::: "memory");
     }

@@ -80,3 +80,29 @@ def test_observations_only_global(n, prec, tol_inner):
     for k in range(N):
         ref = observe(op, solve(op, synthesize(op, x[k], n), n), n)
         assert np.abs(G[k].cpu().numpy() - ref).max() <= 1e-9 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("n", [64, 128])
+def test_kept_state_on_any_double(n):
+    """The kept solution and the gradient from it do not depend on where the caller's buffer starts."""
+    from paper_2503_16028_amd import smc
+    print("[case] kept state alignment", n, flush=True)
+    d = json.load(open(golden("problem_t2.json")))
+    d.update(grids=[n], obs_den=n, obs=corners(n), y=[0.0] * 64, f=1.0, sigma=1.0)
+    op = OProblem(d)
+    N = 3
+    p = smc.Problem(d, N, tol64=1e-10, tol_inner=1e-3)
+    xi = torch.tensor(inputs.particles(N, op.K, 63), device=DEV)
+    got = []
+    for off in (0, 1):
+        G = torch.empty(N, 64, dtype=torch.float64, device=DEV)
+        buf = torch.full((N * n * n + 2,), 7.0, dtype=torch.float64, device=DEV)
+        w = buf[off:off + N * n * n].view(N, n * n)
+        phi, grad = torch.empty(N, dtype=torch.float64, device=DEV), torch.empty(N, op.K, dtype=torch.float64, device=DEV)
+        smc.smc_forward_state(p, N, xi, smc.SMC_FP32_REFINE, G, w)
+        smc.smc_value_and_grad(p, N, xi, smc.SMC_FP32_REFINE, w, phi, grad)
+        torch.cuda.synchronize()
+        assert smc.smc_status_flags(p) == 0
+        assert (buf[:off] == 7.0).all() and (buf[off + N * n * n:] == 7.0).all()
+        got.append((G, w.clone(), phi, grad))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
