@@ -416,6 +416,12 @@ int smc_gather(int64_t N, int32_t K, const int32_t* idx, const double* xi_in,
  * padding and must hold 0 in r.  Grids of 32, 64, 128 and 256 intervals. */
 int smc_precond_apply(smc_problem p, int32_t level, int64_t N, const float* r, float* z, smc_stream stream);
 
+/* The same transform as the solver with its vectors in memory runs it between two iterations (for
+ * tests; grids of 128 and 256 intervals): r enters at the scale of a residual of norm `before`
+ * (positive), as the solver stages it before the norm after the update is known. */
+int smc_precond_apply_staged(smc_problem p, int32_t level, int64_t N, const float* r, double before, float* z,
+                             smc_stream stream);
+
 /* Tile shape of the fast-Poisson solver of a grid (FP32+refinement, single-grid calls): grid rows
  * per thread, so that one particle's workgroup has n*n/rows threads.  Different shapes give the
  * same solution up to rounding (the reduction order changes).

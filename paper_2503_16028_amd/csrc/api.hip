@@ -1291,6 +1291,19 @@ extern "C" int smc_precond_apply(smc_problem p, int32_t level, int64_t N, const 
     return SMC_OK;
 }
 
+extern "C" int smc_precond_apply_staged(smc_problem p, int32_t level, int64_t N, const float* r, double before,
+                                        float* z, smc_stream stream) {
+    if (!p) return fail(SMC_E_INVAL, "problem is NULL");
+    if (int rc = check_n(p->P, N)) return rc;
+    if (level < 0 || level >= p->P.n_levels) return fail(SMC_E_INVAL, "level %d out of range", level);
+    const Level& L = p->P.lv[level];
+    if (!L.dst_S || (L.n != 128 && L.n != 256)) return fail(SMC_E_INVAL, "grid %d stages no residual", L.n);
+    if (!(before > 0.0) || !std::isfinite(before)) return fail(SMC_E_INVAL, "before must be positive");
+    if (N > 0 && (!r || !z)) return fail(SMC_E_INVAL, "r and z must not be NULL");
+    HIPCHK(launch_dst_staged(L.n, N, r, before, z, L.dst_S, L.dst_lam, (hipStream_t)stream));
+    return SMC_OK;
+}
+
 extern "C" int smc_temper(int64_t N, const double* phi, const double* tau_in, double ess_frac, double* h,
                           double* tau_new, double* W, double* log_z_inc, int32_t* flags, smc_stream stream) {
     if (N < 1 || N > (1 << 20)) return fail(SMC_E_INVAL, "N must be 1..2^20");

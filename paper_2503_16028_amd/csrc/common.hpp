@@ -336,6 +336,10 @@ hipError_t launch_solve2d_dst64_onchip(int n, int64_t N, const SolveArgs& a, con
                                        hipStream_t s);
 hipError_t launch_dst_apply(int n, int64_t N, const float* r, float* z, const void* S, const float* lam,
                             hipStream_t s);
+// The transform of the global-memory solver between two iterations (grids of 128 and 256 intervals), for tests: r
+// staged at the scale of a residual of norm `before`.
+hipError_t launch_dst_staged(int n, int64_t N, const float* r, double before, float* z, const void* S, const float* lam,
+                             hipStream_t s);
 
 hipError_t launch_prior(int64_t N, int K, uint64_t seed, uint64_t ctr, double* xi, hipStream_t s);
 hipError_t launch_potential(int64_t N, int n_obs, const double* G, const double* y, double inv2s2, double* phi,

@@ -1614,8 +1614,8 @@ __device__ __forceinline__ vec4_t<T> fma4(T a, vec4_t<T> b, vec4_t<T> c) {
 // The transform that ends in the next search direction, p = z + (r.z / rz) pc (p = z without pc), and
 // returns r.z.  With S symmetric, r.z = r.S (S r S) / lam S is the sum of (S r S)^2 / lam over the
 // modes, known half way, in FP32 from the matrix units' accumulators: the residual is not read again, and z, with beta in
-// hand before its last product, is neither written nor read.  A residual that overflows the staged scale gives a
-// sum that is not finite: p is then left alone.
+// hand before its last product, is neither written nor read.  That sum says nothing of an overflow in FP16 after it:
+// call dstg_next, which looks at the staged scale first.
 // Inlined (a call saves a third of the registers to memory), with the thread's index opaque, so that no
 // address of it is kept through the loop over the iterations.
 __shared__ double g_dst_red[16];
@@ -1662,7 +1662,6 @@ __device__ __forceinline__ double dstg_direction(const T* r, T* p, const T* pc, 
 #pragma unroll
             for (int w = 0; w < 16; ++w) sum += g_dst_red[w];
             sum = uniform(ldexp(sum, 2 * ex));
-            if (!(fabs(sum) < INFINITY)) break;
             beta = pc ? (T)(sum / rz) : T(0);
         }
         float part = 0.f;
@@ -1713,6 +1712,51 @@ __device__ __forceinline__ double dstg_direction(const T* r, T* p, const T* pc, 
     }
     __syncthreads();   // p complete for every thread of the workgroup, and X free
     return sum;
+}
+
+// The direction of the residual r, rr = |r|^2.  `staged`: X holds it at the scale 2^-ex of its norm before the
+// update.  S being orthonormal, every intermediate is bounded by the staged norm, and by it over 2 lam_0 once divided by the
+// eigenvalues; where that bound leaves FP16 (65504, with a factor of two for its rounding: a residual that has
+// grown some 20-fold at 256^2, 80-fold at 128^2, since its scale was taken) r is staged anew from memory.
+template <int NN, typename T>
+__device__ __forceinline__ double dstg_next(const T* r, T* p, const T* pc, double rz, const _Float16* S, int staged,
+                                            int& ex, double rr) {
+    const double top = 2.0 * 32768.0 * (double)g_dst_lam[0];
+    if (!staged || !(ldexp(rr, -2 * ex) < top * top)) {
+        staged = 0;
+        ex = norm_exponent(rr) + 3;
+    }
+    return dstg_direction<NN, T>(r, p, pc, rz, S, staged, ex);
+}
+
+// The same alone, for tests: z = L^{-1} r of each grid, r staged at the scale of a residual of norm `before`.
+template <int NN>
+__global__ __launch_bounds__(1024) void dstg_next_kernel(const float* __restrict__ rin, float* __restrict__ zout,
+                                                         const _Float16* __restrict__ Stab,
+                                                         const float* __restrict__ lamtab, double before) {
+    __shared__ double red[16];
+    _Float16* X = reinterpret_cast<_Float16*>(g_mixed_smem);
+    const float* r = rin + (int64_t)blockIdx.x * NN * NN;
+    if (threadIdx.x < NN) g_dst_lam[threadIdx.x] = lamtab[threadIdx.x];
+    int ex = norm_exponent(before * before) + 3;
+    const float sc = ldexpf(1.0f, -ex);
+    double acc = 0.0;
+    for (int k = threadIdx.x; k < NN * NN; k += 1024) {
+        acc += (double)r[k] * (double)r[k];
+        X[(k / NN) * (NN + 8) + k % NN] = (_Float16)(r[k] * sc);
+    }
+    const double rr = block_sum<16>(acc, red);   // its barrier publishes X and the eigenvalues
+    dstg_next<NN, float>(r, zout + (int64_t)blockIdx.x * NN * NN, nullptr, 1.0, Stab, 1, ex, rr);
+}
+
+hipError_t launch_dst_staged(int n, int64_t N, const float* r, double before, float* z, const void* S, const float* lam,
+                             hipStream_t s) {
+    if (N <= 0) return hipSuccess;
+    const _Float16* Sh = reinterpret_cast<const _Float16*>(S);
+    if (n == 128) dstg_next_kernel<128><<<dim3((unsigned)N), dim3(1024), 0, s>>>(r, z, Sh, lam, before);
+    else if (n == 256) dstg_next_kernel<256><<<dim3((unsigned)N), dim3(1024), 0, s>>>(r, z, Sh, lam, before);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 __global__ __launch_bounds__(1024) void dst256_apply_kernel(const float* __restrict__ rin, float* __restrict__ zout,
@@ -2308,13 +2352,8 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
                 if (np == NP) fold();
                 T* pn = pb + np * nodes;
                 const T* before = w_now ? nullptr : pc;   // w0 is no preconditioned residual: its beta follows
-                double rzn;
-                for (int staged = it > 0;; staged = 0) {
-                    rzn = dstg_direction<NN, T>(rv, pn, before, rz, Stab, staged, ex);
-                    ++napp;
-                    if (fabs(rzn) < INFINITY || !staged) break;
-                    ex = norm_exponent(rr) + 3;   // the residual outgrew the staged scale: redo from r
-                }
+                const double rzn = dstg_next<NN, T>(rv, pn, before, rz, Stab, it > 0, ex, rr);
+                ++napp;
                 if (w_now) {   // conjugate to w0 by the definition
                     double zq = 0.0;
 #pragma unroll 2

@@ -102,6 +102,7 @@ _SIGS = {
     "smc_resample": (c_i32, [c_i64, c_vp, c_u64, c_vp, c_vp, c_vp]),
     "smc_gather": (c_i32, [c_i64, c_i32, c_vp, c_vp, c_vp, c_vp, c_vp, c_vp]),
     "smc_precond_apply": (c_i32, [c_vp, c_i32, c_i64, c_vp, c_vp, c_vp]),
+    "smc_precond_apply_staged": (c_i32, [c_vp, c_i32, c_i64, c_vp, c_dbl, c_vp, c_vp]),
     "smc_profile": (c_i32, [c_vp, c_i32]),
     "smc_profile_read": (c_i32, [c_vp, c_vp, ctypes.POINTER(c_dbl), ctypes.POINTER(c_i64), ctypes.POINTER(c_i64),
                                  ctypes.POINTER(c_i64), ctypes.POINTER(c_i64), ctypes.POINTER(c_i64)]),
@@ -537,3 +538,9 @@ def smc_precond_apply(problem, level, N, r, z, stream=None):
     n = problem.grids[level]
     _check(lib().smc_precond_apply(problem.handle, int(level), N, _ptr(r, torch.float32, N * n * n, "r"),
                                    _ptr(z, torch.float32, N * n * n, "z"), _stream(stream)))
+
+
+def smc_precond_apply_staged(problem, level, N, r, before, z, stream=None):
+    n = problem.grids[level]
+    _check(lib().smc_precond_apply_staged(problem.handle, int(level), N, _ptr(r, torch.float32, N * n * n, "r"),
+                                          float(before), _ptr(z, torch.float32, N * n * n, "z"), _stream(stream)))

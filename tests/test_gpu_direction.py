@@ -1,0 +1,53 @@
+"""The transform of the solver with its vectors in memory, on a residual that has grown since its scale was
+taken (GPU): between two iterations the residual is staged in FP16 at the scale of its norm before the
+update, and one that has outgrown the scale must be staged anew.
+
+Tolerance: that of the preconditioner's own test, 4e-3 of the largest value, from FP16 operands (2^-11 each) in
+four products; the scale is a power of two, so at unchanged precision it adds nothing.
+"""
+import json
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import inputs
+from conftest import golden
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def reference(r, n):
+    a = np.arange(1, n)
+    S = np.sqrt(2.0 / n) * np.sin(np.pi * np.outer(a, a) / n)
+    lam = np.sin(np.pi * a / (2 * n)) ** 2
+    return S @ ((S @ r[:n - 1, :n - 1] @ S) / (lam[:, None] + lam[None, :])) @ S
+
+
+@pytest.mark.parametrize("n", [128, 256])
+@pytest.mark.parametrize("growth", [1.0, 5.0, 45.0, 300.0, 5000.0, 1e7])
+def test_residual_that_outgrew_its_scale(n, growth):
+    from paper_2503_16028_amd import smc
+    print("[case] staged transform", n, growth, flush=True)
+    sys.stdout.flush()
+    d = json.load(open(golden("problem_t2.json")))
+    d.update(grids=[n])
+    p = smc.Problem(d, 3)
+    s = np.sin(np.pi * np.arange(1, n + 1) / n)
+    r = np.zeros((3, n, n), dtype=np.float32)
+    r[0] = np.outer(s, s)                                        # the lowest mode: the largest quotient
+    r[1] = np.outer(s, np.sin(3 * np.pi * np.arange(1, n + 1) / n))
+    r[2] = inputs.particles(n, n, 5)
+    r[:, n - 1, :] = 0.0
+    r[:, :, n - 1] = 0.0
+    r /= np.sqrt((r.astype(np.float64) ** 2).sum((1, 2)))[:, None, None]
+    z = torch.empty(3, n, n, dtype=torch.float32, device=DEV)
+    smc.smc_precond_apply_staged(p, 0, 3, torch.tensor(r, device=DEV), 1.0 / growth, z)
+    torch.cuda.synchronize()
+    got = z.cpu().numpy()
+    for k in range(3):
+        ref = reference(r[k].astype(np.float64), n)
+        assert np.abs(got[k, :n - 1, :n - 1] - ref).max() <= 4e-3 * np.abs(ref).max(), k
+        assert not got[k, n - 1].any() and not got[k, :, n - 1].any()
