@@ -2088,20 +2088,20 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
 //   - keeps its search direction in a buffer of its own instead of adding it to x: the correction is
 //     sum alpha_k p_k once at the end of the sweep (directions are folded into x when the buffers are
 //     used up), so x is not touched per iteration;
-//   - gets its direction from the transform (dstg_direction), which has r.z before its last product, so z
+//   - gets its direction from the transform (dstg_next), which has r.z before its last product, so z
 //     stays in registers;
 //   - keeps q = A p in registers from the product with A to the residual's update (the same thread, the
 //     same nodes);
 //   - runs down bands of rows, the neighbours above and below carried in registers, the horizontal ones taken
 //     from the adjacent lanes;
-// and moves p twice, r twice, t and the direction before: 6 vector passes, where cg_global_body has 13 and a
-// version with z and q in memory 10.
+// and moves p twice, r twice, t and the direction before: 6 vector passes (FP64: 7, r once more), where
+// cg_global_body has 13 and a version with z and q in memory 10.
 // A refinement step rounds dx = D^{-1/2} y to T and updates the FP64 residual, as strip_refine does; the
 // FP64 passes run down columns, the vertical neighbours carried in registers.  The passes over the
 // vectors keep a few loads in flight per thread and leave the rest to the sixteen waves: unrolled
 // further they spill, and scratch traffic is what this solver can least afford.  Measured, with 13, 10 and
-// 6 passes: 1024 solves at 256^2 in FP32 10.70, 7.73 and 5.4 ms; 32 solves 1.45, 0.93 and
-// 0.72; 1001 at 128^2 in FP64 2.77, 2.63 and 1.90.
+// 6 (7) passes: 1024 solves at 256^2 in FP32 10.70, 7.73 and 5.5 ms; 32 solves 1.45, 0.93 and
+// 0.79; 1001 at 128^2 in FP64 2.77, 2.63 and 2.08.
 // Vector slots of a particle's row of a.vec (7 n^2 doubles): t, r, q, then the directions; FP32 has
 // the last one for x, FP64 keeps x in a.aux.
 template <typename T, int NN>
@@ -2377,10 +2377,11 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
             const T sc = (T)ldexpf(1.0f, -ex);
             V4 q[QREG ? RB : 1];
             T pq_acc = T(0);
+            double rp_acc = 0.0;
             {
                 uint32_t at = (uint32_t)(k0 * sizeof(T));
                 asm volatile("" : "+v"(at));   // else every row's addresses are kept in registers, and spill
-                const gcbp pB = uniform_base(pc), tB = uniform_base(tv), qB = uniform_base(qv);
+                const gcbp pB = uniform_base(pc), tB = uniform_base(tv), qB = uniform_base(qv), rB = uniform_base(rv);
                 V4 p4 = at_off<V4>(pB, at), t4 = at_off<V4>(tB, at);
                 V4 yS = {T(0), T(0), T(0), T(0)};   // t p of the row below
                 if (g0 > 0) yS = at_off<V4>(tB, at - ROW) * at_off<V4>(pB, at - ROW);
@@ -2390,6 +2391,8 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
                     const int g = g0 + i;   // past the last row its own again (unused)
                     const uint32_t up = at + (g < NN - 1 ? ROW : 0);
                     const V4 pN = at_off<V4>(pB, up), tN = at_off<V4>(tB, up);
+                    V4 r4;
+                    if constexpr (!F32) r4 = at_off<V4>(rB, at);
                     const V4 yN = tN * pN;
                     // the nodes beyond the four, from the adjacent lanes: at a row's start the lane before
                     // ends in the padding column, where every direction is zero
@@ -2401,6 +2404,7 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
                         const T yW = (m > 0) ? yc[m > 0 ? m - 1 : 0] : yW0;
                         qi[m] = interior(g, cc + m) ? p4[m] - t4[m] * ((yE + yW) + (yN[m] + yS[m])) : T(0);
                         pq_acc += p4[m] * qi[m];
+                        if constexpr (!F32) rp_acc += p4[m] * r4[m];
                     }
                     p4 = pN;
                     t4 = tN;
@@ -2408,17 +2412,25 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
                     yc = yN;
                     // a row at a time: the compiler would load them all first, and spill
                     asm volatile("" : "+v"(qi[0]), "+v"(qi[1]), "+v"(qi[2]), "+v"(qi[3]), "+v"(pq_acc)::"memory");
+                    if constexpr (!F32) asm volatile("" : "+v"(rp_acc)::"memory");
                     if constexpr (QREG) q[i] = qi;
                     else put_off<V4>(qB, at, qi);
                     at += ROW;
                 }
             }
+            // In FP64 the step length takes r.p from the vectors: the transform's r.z, of operands in FP16,
+            // would make each line search inexact, and one sweep runs to 1e-11.  On fields without decay
+            // (545 iterations at 128^2 with r.z from z) the solve took 597 without this and takes 556, for a
+            // seventh pass (1001 solves at 128^2 1.91 -> 2.08 ms).  In FP32, to 1e-3 a sweep, it
+            // changes nothing (805 and 811 iterations at 256^2).
+            double rp = rz;
+            if constexpr (!F32) rp = block_sum<NW>(rp_acc, red2);
             pq = block_sum<NW>((double)pq_acc, red1);
             if (!(pq > 0.0) || !(pq < INFINITY)) {
                 broke = true;
                 break;
             }
-            const T alpha = (T)(rz / pq);
+            const T alpha = (T)(rp / pq);
             if (tid == 0) alphas[np] = alpha;
             T r_acc = T(0);
             {
