@@ -612,8 +612,7 @@ __device__ __noinline__ double pair_refine(const double* __restrict__ e_, double
     constexpr int NP1 = NN + 1, PAD = NN + 1, RB = NN * NN / 2 / NT, B = RB < 4 ? RB : 4;
     typedef T T2 __attribute__((ext_vector_type(2)));
     typedef SD SD2 __attribute__((ext_vector_type(2)));
-    typedef double D2 __attribute__((ext_vector_type(2)));
-    typedef double D2U __attribute__((ext_vector_type(2), aligned(8)));   // rows of e start on any double
+    typedef double D2U __attribute__((ext_vector_type(2), aligned(8)));   // rows of e and r start on any double
     typedef __attribute__((address_space(3))) T* ltp;
     typedef __attribute__((address_space(3))) T2* ltp2;
     const double n2 = (double)NN * (double)NN;
@@ -628,8 +627,7 @@ __device__ __noinline__ double pair_refine(const double* __restrict__ e_, double
     SD2 sv[RB];
 #pragma unroll
     for (int r = 0; r < RB; ++r) sv[r] = at_off<SD2>(sd + r * NN * (int)sizeof(SD), (uint32_t)c * (uint32_t)sizeof(SD));
-    D2U eN[B];
-    D2 ro[B];
+    D2U eN[B], ro[B];
     double eW0[B];
     auto load = [&](int blk) __attribute__((always_inline)) {
 #pragma unroll
@@ -638,11 +636,11 @@ __device__ __noinline__ double pair_refine(const double* __restrict__ e_, double
             const int up = g0 + r < NN - 1 ? r + 1 : r;   // past the last row its own (unused)
             eN[k] = at_off<D2U>(e + up * NP1 * 8, eo);
             eW0[k] = SE ? eu[r * NP1] : at_off<double>(e + r * NP1 * 8, 0u);
-            ro[k] = D2{f, f};
+            ro[k] = D2U{f, f};
         }
         if (!first) {
 #pragma unroll
-            for (int k = 0; k < B; ++k) ro[k] = at_off<D2>(rb + (blk * B + k) * NN * 8, ro_);
+            for (int k = 0; k < B; ++k) ro[k] = at_off<D2U>(rb + (blk * B + k) * NN * 8, ro_);
         }
     };
     D2U eS = at_off<D2U>(e - NP1 * 8, eo), eC = at_off<D2U>(e, eo);
@@ -684,7 +682,7 @@ __device__ __noinline__ double pair_refine(const double* __restrict__ e_, double
             const double dW = (double)xW[k], dE = (double)xE[k], dN0 = (double)x0[k], dN1 = (double)x1[k];
             const double flux0 = eC[1] * (d0 - d1) + eW * (d0 - dW) + en[0] * (d0 - dN0) + eS[0] * (d0 - dS0);
             const double flux1 = eE * (d1 - dE) + eC[0] * (d1 - d0) + en[1] * (d1 - dN1) + eS[1] * (d1 - dS1);
-            D2 res;
+            D2U res;
             res[0] = ro[k][0] - eC[0] * n2 * flux0;
             res[1] = ro[k][1] - eC[1] * n2 * flux1;
             const bool row = g0 + r < NN - 1;   // uniform
@@ -693,7 +691,7 @@ __device__ __noinline__ double pair_refine(const double* __restrict__ e_, double
             acc += res[0] * res[0];
             acc += res[1] * res[1];
             asm volatile("" : "+v"(acc), "+v"(res)::"memory");   // a row at a time: the compiler would hold many, and spill
-            put_off<D2>(rb + r * NN * 8, ro_, res);
+            put_off<D2U>(rb + r * NN * 8, ro_, res);
             T2 o;
             o[0] = (T)((double)sv[r][0] * res[0]);
             o[1] = (T)((double)sv[r][1] * res[1]);
