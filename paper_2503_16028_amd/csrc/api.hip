@@ -66,17 +66,13 @@ static void free_problem(Problem& P) {
     f(P.ws_v); f(P.ws_logr); f(P.ws_phinew); f(P.ws_e); f(P.ws_x64); f(P.ws_lam); f(P.ws_gnew); f(P.ws_sd);
     f(P.ws_vec);
     f(P.ws_G); f(P.ws_iters); f(P.ws_list); f(P.ws_counters); f(P.flags); f(P.stats);
-    f(P.ws_fit_d2); f(P.ws_fit_par); f(P.ws_fit_part); f(P.ws_fit_tiles); f(P.ws_fit_centers); f(P.ws_mixtab);
+    f(P.ws_fit_d2); f(P.ws_fit_par); f(P.ws_fit_part); f(P.ws_fit_centers); f(P.ws_mixtab);
     f(P.mix_c);
 }
 
-// The fit's tiles of the cloud; a problem that leaves no room for them fits from the rows.
-static void alloc_fit_tiles(Problem& P) {
-    if (hipMalloc((void**)&P.ws_fit_tiles, sizeof(double) * em_blocks(P.n_max) * 64 * P.kr) != hipSuccess) {
-        P.ws_fit_tiles = nullptr;
-        (void)hipGetLastError();
-    }
-}
+// Doubles of the proposal rows, which a fit uses as the tiles of its cloud: no proposal outlives a call, and calls on
+// one problem do not overlap.
+static int64_t rows_or_tiles(const Problem& P) { return std::max(P.n_max * P.K, em_blocks(P.n_max) * 64 * P.kr); }
 
 extern "C" const char* smc_last_error(void) { return g_err.c_str(); }
 
@@ -273,7 +269,7 @@ extern "C" int smc_problem_create(const smc_problem_desc* d, smc_problem* out) {
     P.x_stride = P.e_stride;
     P.vec_stride = P.dim == 2 ? 7 * nb * nb : 0;
     const int64_t Nm = P.n_max;
-    ck(hipMalloc((void**)&P.ws_v, sizeof(double) * Nm * K));
+    ck(hipMalloc((void**)&P.ws_v, sizeof(double) * rows_or_tiles(P)));
     ck(hipMalloc((void**)&P.ws_logr, sizeof(double) * Nm));
     ck(hipMalloc((void**)&P.ws_phinew, sizeof(double) * Nm));
     ck(hipMalloc((void**)&P.ws_e, sizeof(double) * Nm * P.e_stride));
@@ -296,7 +292,6 @@ extern "C" int smc_problem_create(const smc_problem_desc* d, smc_problem* out) {
         ck(hipMalloc((void**)&P.ws_fit_part, sizeof(double) * em_blocks(Nm) * pe));
         ck(hipMalloc((void**)&P.ws_fit_centers, sizeof(int32_t) * MAX_M));
         ck(hipMalloc((void**)&P.ws_mixtab, sizeof(double) * MAX_LEVELS * MIXTAB));
-        if (e == hipSuccess) alloc_fit_tiles(P);
     }
     ck(hipMalloc((void**)&P.flags, sizeof(int32_t)));
     ck(hipMalloc((void**)&P.stats, 4 * sizeof(unsigned long long)));
@@ -355,7 +350,7 @@ extern "C" int smc_problem_create_l2mix(const smc_l2mix_desc* d, smc_problem* ou
     ck(upload(&P.slot, slot.data(), slot.size()));
     ck(upload(&P.mix_c, d->c, (size_t)P.n_terms * P.K));
     const int64_t Nm = P.n_max;
-    ck(hipMalloc((void**)&P.ws_v, sizeof(double) * Nm * P.K));
+    ck(hipMalloc((void**)&P.ws_v, sizeof(double) * rows_or_tiles(P)));
     ck(hipMalloc((void**)&P.ws_logr, sizeof(double) * Nm));
     ck(hipMalloc((void**)&P.ws_phinew, sizeof(double) * Nm));
     ck(hipMalloc((void**)&P.ws_iters, sizeof(int32_t) * Nm));
@@ -364,7 +359,6 @@ extern "C" int smc_problem_create_l2mix(const smc_l2mix_desc* d, smc_problem* ou
     ck(hipMalloc((void**)&P.ws_fit_part, sizeof(double) * em_blocks(Nm) * MAX_M * (1 + 2 * MAX_KR)));
     ck(hipMalloc((void**)&P.ws_fit_centers, sizeof(int32_t) * MAX_M));
     ck(hipMalloc((void**)&P.ws_mixtab, sizeof(double) * MAX_LEVELS * MIXTAB));
-    if (e == hipSuccess) alloc_fit_tiles(P);
     ck(hipMalloc((void**)&P.flags, sizeof(int32_t)));
     ck(hipMalloc((void**)&P.stats, 4 * sizeof(unsigned long long)));
     ck(hipMemset(P.stats, 0, 4 * sizeof(unsigned long long)));
@@ -878,7 +872,7 @@ extern "C" int smc_gm_fit(smc_problem p, int64_t N, const double* xi, int32_t M,
     if (iters < 0 || iters > 100000) return fail(SMC_E_INVAL, "iters must be 0..100000");
     if (!(var_floor > 0.0) || !std::isfinite(var_floor)) return fail(SMC_E_INVAL, "var_floor must be positive");
     if (!xi || !logw || !mean || !scale) return fail(SMC_E_INVAL, "xi, logw, mean and scale must not be NULL");
-    FitWorkspace w{P.ws_fit_d2, P.ws_fit_par, P.ws_fit_part, P.ws_fit_tiles};
+    FitWorkspace w{P.ws_fit_d2, P.ws_fit_par, P.ws_fit_part, P.ws_v};
     HIPCHK(launch_gm_fit(N, P.K, P.kr, P.active, xi, M, iters, var_floor, seed, ctr, w,
                          centers ? centers : P.ws_fit_centers, logw, mean, scale, (hipStream_t)stream));
     return SMC_OK;
@@ -1050,7 +1044,7 @@ static int sampler_stage(smc_problem_s* p, const smc_sampler_graph_desc* d, int3
         HIPCHK(hipMemcpyAsync(d->phi + o, d->phi2 + o, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
         HIPCHK(hipMemcpyAsync(d->tau + g, d->tau_new + g, sizeof(double), hipMemcpyDeviceToDevice, s));
         if (M > 1) {
-            FitWorkspace w{P.ws_fit_d2, P.ws_fit_par, P.ws_fit_part, P.ws_fit_tiles};
+            FitWorkspace w{P.ws_fit_d2, P.ws_fit_par, P.ws_fit_part, P.ws_v};
             HIPCHK(launch_gm_fit_ctr(n, K, kr, P.active, d->xi + o * K, M, d->fit_iters, d->var_floor, d->seed, ctr,
                                      (uint64_t)g, w, P.ws_fit_centers, d->logw + (int64_t)g * M,
                                      d->mean + (int64_t)g * M * kr, d->scale + (int64_t)g * M * kr, s));

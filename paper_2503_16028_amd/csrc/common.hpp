@@ -51,7 +51,7 @@ struct Problem {
     int32_t active_h[MAX_KR];
     double* y = nullptr;         // [n_obs]
     // workspace, all for n_max particles
-    double* ws_v = nullptr;      // [n_max][K]    proposals
+    double* ws_v = nullptr;      // [n_max][K]    proposals; during a fit [workgroups of 64 particles][kr][64], its tiles
     double* ws_logr = nullptr;   // [n_max]       log R of the proposal
     double* ws_phinew = nullptr; // [n_max]       potential of the proposal
     double* ws_e = nullptr;      // [n_max][(n_big+1)^dim]  exp(u/2) at the nodes
@@ -68,7 +68,6 @@ struct Problem {
     double* ws_fit_d2 = nullptr;      // [n_max]   squared distance to the nearest seeded centre
     double* ws_fit_par = nullptr;     // [2][GM_PAR]  EM parameter blocks (ping-pong)
     double* ws_fit_part = nullptr;    // [workgroups of 64 particles][MAX_M][1 + 2 MAX_KR]  partial sums
-    double* ws_fit_tiles = nullptr;   // [workgroups of 64 particles][kr][64]  the cloud's active coordinates
     int32_t* ws_fit_centers = nullptr;  // [MAX_M] seeded rows
     double* ws_mixtab = nullptr;      // [MAX_LEVELS][MIXTAB]  mixture tables of the proposal, per group
     int n_cu = 0;                // compute units of the device
@@ -372,7 +371,7 @@ struct FitWorkspace {
     double* d2;
     double* par;
     double* part;
-    double* tiles;   // may be nullptr
+    double* tiles;   // [workgroups of 64 particles][kr][64] for the active coordinates, or nullptr
 };
 int64_t em_blocks(int64_t N);
 // Mixture fit on the library's static scratch array (no allocation), for up to STATIC_FIT_N
