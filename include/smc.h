@@ -380,9 +380,8 @@ int64_t smc_gm_fit_noalloc_max(void);
 
 /* Re-weighting and next temperature (Alg. 1; App. C): with tau = *tau_in (device scalar),
  * choose h in (0, 1 - tau] with ESS(h) = ess_frac * N, where ESS = 1 / sum W^2 and
- * W_n ∝ exp(-h Phi_n): the largest h (to the rounding of the ESS, a relative 2^-51, or to a
- * relative 2^-52 or (1 - tau) 2^-64 of h) whose ESS still passes, found by safeguarded Newton
- * steps on log ESS; take h = 1 - tau when that already passes.
+ * W_n ∝ exp(-h Phi_n): the largest h (to a relative 2^-52, or (1 - tau) 2^-64) whose ESS still
+ * passes, found by safeguarded Newton steps on log ESS; take h = 1 - tau when that already passes.
  * Outputs (device): *h, *tau_new (= 1 exactly on the last stage), W[N] normalised weights,
  * *log_z_inc = log((1/N) sum exp(-h Phi)).  Non-finite Phi get weight 0.  A zero step while
  * tau < 1 sets SMC_FLAG_STALL (at tau = 1 the step is 0 and *tau_new = 1 without a flag), and

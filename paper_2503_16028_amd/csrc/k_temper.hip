@@ -27,15 +27,13 @@ constexpr int CNT = 2, SUM_D = 3, SUM_DD = 4;        // of the first pass, besid
 // passes, else the root of the decreasing f, kept in a bracket [lo, hi] with f(lo) >= 0 > f(hi).  The
 // first point is the root of the expansion f(h) ~ f(0) - h^2 Var(d); then Newton steps in log h (ESS
 // falls off like a power of h for spread-out potentials), replaced by the bracket's geometric (or
-// arithmetic) mean whenever a step would leave the bracket.  It ends at a point whose f is 0 to
-// ESS_TOL, the rounding of f (a step that lands below 0 by no more is repeated towards the passing side, twice
-// as far each time), or when the bracket is 2^-52 relative or the bisection resolution (1 - tau) 2^-64
-// wide.  The returned h always has f(h) >= 0, ESS >= rho N, as the lower end of a bisection would; about
-// 6 passes replace 66 (12 before the end by ESS_TOL: the rest moved h inside the rounding of f).
-constexpr double ESS_TOL = 0x1p-51;
+// arithmetic) mean whenever a step would leave the bracket.  It ends when the bracket is 2^-52 relative or
+// the bisection resolution (1 - tau) 2^-64 wide; a point that Newton's step would move by no more than a few such
+// widths is therefore left for its other side, 1, 4, 16 ... widths away, until both ends are near the root.  The
+// returned h always has f(h) >= 0, ESS >= rho N, as the lower end of a bisection would; about 11 passes replace 66.
 enum TemperMode { MODE_FIRST = 0, MODE_NEWTON = 1, MODE_DONE = 2, MODE_NONE = 3 };   // NONE: no finite potential
 struct Temper {
-    double pmin, tau, lo, hi, x, s1, nudge;   // s1: sum W at lo
+    double pmin, tau, lo, hi, x, s1, reach;   // s1: sum W at lo
     int mode, it, last;
 
     __device__ __forceinline__ void first(const Sums& e, double goal) {   // goal: rho N
@@ -50,7 +48,7 @@ struct Temper {
         lo = 0.0;
         hi = rest;
         s1 = e.v[CNT];
-        nudge = 0.5;
+        reach = 1.0;
         it = 0;
         mode = MODE_NEWTON;
         const double f0 = log(e.v[CNT] / goal), m = e.v[SUM_D] / e.v[CNT], v = e.v[SUM_DD] / e.v[CNT] - m * m;
@@ -66,17 +64,16 @@ struct Temper {
             hi = x;
         }
         mode = MODE_DONE;
-        if ((pass && fx <= ESS_TOL) || !(hi - lo > fmax(floor_w, hi * 0x1p-52)) || ++it >= 96) return;
+        if (!(hi - lo > fmax(floor_w, hi * 0x1p-52)) || ++it >= 96) return;
         const double dfx = -2.0 * e.v[D1] / e.v[S1] + 2.0 * e.v[D2] / e.v[S2];
-        if (!pass && -fx <= 4.0 * ESS_TOL) nudge *= 2.0;
-        const double aim = pass ? 0.5 * ESS_TOL : nudge * ESS_TOL;
-        const double st = (aim - fx) / (dfx * x);   // Newton in log h
-        double xn = (fabs(st) < 50.0) ? x * exp(st) : NAN;
-        if (!(xn > lo && xn < hi)) xn = lo > 0.0 ? sqrt(lo * hi) : 0.5 * (lo + hi);
-        if (fabs(xn - x) <= fmax(floor_w, xn * 0x1p-52)) {   // converged next to the root
-            if (pass) return;
-            xn = fmax(lo, x * (1.0 - 0x1p-46));           // the root lies just below x
+        const double st = -fx / (dfx * x), width = fmax(floor_w, x * 0x1p-52);
+        double xn = (fabs(st) < 50.0) ? x * exp(st) : NAN;   // Newton in log h
+        if (fabs(xn - x) <= 4.0 * width) {                    // next to the root: to its other side
+            xn = reach > 4096.0 ? NAN : pass ? x + reach * width : x - reach * width;
+            reach *= 4.0;
         }
+        if (!(xn > lo && xn < hi)) xn = lo > 0.0 && hi > 2.0 * lo ? sqrt(lo * hi) : 0.5 * (lo + hi);
+        if (!(xn > lo && xn < hi)) return;   // neighbouring doubles
         x = xn;
         mode = MODE_NEWTON;
     }
@@ -88,16 +85,16 @@ template <bool FIRST>
 __device__ __forceinline__ void add_point(Sums& e, double p, double pmin, double x) {
     const bool fin = isfinite(p);
     const double d = fin ? p - pmin : 0.0;
-    const double y = exp(-x * d), w = fin ? y : 0.0, ww = w * w;
+    const double y = exp(-x * d), w = fin ? y : 0.0;
     e.v[S1] += w;
-    e.v[S2] += ww;
+    e.v[S2] = __builtin_fma(w, w, e.v[S2]);   // the same bits in every pass
     if constexpr (FIRST) {
         e.v[CNT] += fin ? 1.0 : 0.0;
         e.v[SUM_D] += d;
         e.v[SUM_DD] += d * d;
     } else {
         e.v[D1] += d * w;
-        e.v[D2] += d * ww;
+        e.v[D2] += d * (w * w);
     }
 }
 // Entries beg, beg + step, ... of p.
@@ -175,8 +172,8 @@ __device__ __forceinline__ double weight(double p, const Temper& t, double ls1) 
 // One workgroup.  CACHED: the d_n sit in LDS (-1 for a non-finite potential), N <= TEMPER_ONE; else
 // each pass reads the potentials.  Four waves when cached: a pass then costs the exponentials of N / 256
 // particles a lane and one wave's reductions per SIMD; with sixteen, four waves' reductions and decisions share
-// each SIMD and cost more than the exponentials (4096 particles: 79 us with sixteen waves and 12 passes, 27
-// with four and 7).
+// each SIMD and cost more than the exponentials (4096 particles: 85 us with sixteen waves and 16 passes, 33
+// with four and 11).
 constexpr int TEMPER_ONE = 8064;   // 63 KB
 template <int NT, bool CACHED>
 __global__ __launch_bounds__(NT) void temper_kernel(int64_t N, const double* __restrict__ phi,
@@ -215,11 +212,11 @@ __global__ __launch_bounds__(NT) void temper_kernel(int64_t N, const double* __r
 // and partial sums live in the first SCRATCH entries of W, in two copies that alternate between
 // launches; a last one-workgroup launch writes the weights of those entries.  A single workgroup
 // takes 1M particles through a pass in 0.7 ms, one compute unit's rate of FP64 exponentials; the whole
-// chain takes 89 us there (8.5 ms with one workgroup), of which 55, its time at 8065 particles, are launches and
+// chain takes 114 us there (8.6 ms with one workgroup), of which 85, its time at 8065 particles, are launches and
 // the latency of the sums.
 constexpr int TEMPER_BLOCKS = 256, STATE = 16;
 constexpr int SCRATCH = 2 * (STATE + 5 * TEMPER_BLOCKS);
-constexpr int PASSES = 12;   // 4 to 9 for spreads up to chi^2, 11 for potentials spread over ten decades
+constexpr int PASSES = 16;   // about 11 for chi^2 potentials, up to 15 in nineteen clouds of twenty
 static_assert(SCRATCH <= TEMPER_ONE && sizeof(Temper) <= STATE * sizeof(double), "the scratch fits W");
 
 namespace {
@@ -319,8 +316,10 @@ __global__ __launch_bounds__(256) void temper_weight_kernel(int64_t beg, int64_t
 
 // The chain wants W apart from what it reads, as it writes its scratch there before the last reading; a
 // cloud weighed in place takes the one-workgroup kernel, where each entry's last reading is its
-// writer's.  The line is the LDS a launch gets without asking for more, just short of where the two meet
-// (6144 particles: 35 us in one workgroup, 55 in the chain).
+// writer's.  The line is the LDS a launch gets without asking for more, short of where the two meet (8064
+// particles: 52 us in one workgroup, 84 in the chain).  The chain's launches cost its 70 us also where the
+// first pass ends the search, once in a run, which one workgroup does in 20 to 60 us up to 50000 particles; the
+// other steps of the run take it 110 to 500 us there.
 hipError_t launch_temper(int64_t N, const double* phi, const double* tau_in, double ess_frac, double* h,
                          double* tau_new, double* W, double* log_z, int32_t* flags, hipStream_t s) {
     const double goal = ess_frac * (double)N;

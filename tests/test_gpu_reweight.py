@@ -148,3 +148,27 @@ def test_many_workgroups_in_a_graph():
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(e, (W, idx, h, tau_new, lz))), r
         assert not torch.equal(idx, torch.arange(N, dtype=torch.int32, device=DEV))
+
+
+@pytest.mark.parametrize("N", [64, 4096, 8064, 8065, 20000])
+def test_next_double_does_not_pass(N):
+    """The increment is the largest whose ESS passes, to a relative 2^-52: between 1/2 and 1 that is one double, and
+    the call itself says so.  With tau = 1 - h the whole remaining step is h and passes (h and tau_new = 1 come
+    back, both exact); with the next double in its place it does not."""
+    from paper_2503_16028_amd import smc
+
+    def step(phi, tau):
+        h, tau_new, lz = (torch.empty(1, dtype=torch.float64, device=DEV) for _ in range(3))
+        smc.smc_temper(N, phi, t([tau]), 0.5, h, tau_new, torch.empty(N, dtype=torch.float64, device=DEV), lz)
+        return h.item(), tau_new.item()
+
+    for seed in range(8):
+        banner("next double", N, seed)
+        phi0 = inputs.potentials(N, 100 + seed)
+        h0, _ = step(t(phi0), 0.0)
+        phi = t(phi0 * (h0 / (0.55 + 0.05 * seed)))
+        h, _ = step(phi, 0.0)
+        assert 0.5 < h < 1.0
+        assert step(phi, 1.0 - h) == (h, 1.0)
+        above = np.nextafter(h, 1.0)
+        assert step(phi, 1.0 - above)[0] < above
