@@ -783,12 +783,14 @@ static int move_loop(smc_problem_s* p, int64_t N, MoveParams q, int32_t n_moves,
                      double* xi, double* phi, int32_t* n_acc, hipStream_t s) {
     const Problem& P = p->P;
     if (N <= 0) return SMC_OK;
-    if (n_moves > 0 && !level && P.kind == KIND_L2MIX && chain_l2mix_supported(P.K)) {
+    if (n_moves > 0 && !level && P.kind == KIND_L2MIX &&
+        chain_l2mix_wanted(N, P.K, P.n_terms, q.M, n_moves)) {
         HIPCHK(launch_chain_l2mix(N, P.K, n_moves, q, P.slot, P.sqrt_lam, P.mix_c, P.n_terms,
                                   0.5 / (P.sigma * P.sigma), xi, phi, n_acc, P.flags, P.n_cu, s));
         return SMC_OK;
     }
-    if (n_moves > 0 && !level && P.kind == KIND_DARCY && P.dim == 1 && chain1d_supported(P.lv[0].n, P.K, q.M)) {
+    if (n_moves > 0 && !level && P.kind == KIND_DARCY && P.dim == 1 &&
+        chain1d_wanted(N, P.lv[0].n, P.K, q.M, n_moves)) {
         const bool rec = P.profiling && !p->capturing;
         if (rec) HIPCHK(record(p->pool, s));
         HIPCHK(launch_chain1d(N, P.K, P.lv[0].n, n_moves, q, P.slot, P.sqrt_lam, P.lv[0].basis, solve_args(P, 0), xi, phi,

@@ -354,11 +354,11 @@ hipError_t prepare_kernels();
 hipError_t prepare_chain_kernels();
 // A whole stage of n_moves pCN-GM moves in one launch (k_chain.hip); n_acc is written, not added to.
 // The mixture and counters are read from q as the step kernels read them; no level map.
-bool chain_l2mix_supported(int K);
+bool chain_l2mix_wanted(int64_t N, int K, int T, int M, int n_moves);
 hipError_t launch_chain_l2mix(int64_t N, int K, int n_moves, const MoveParams& q, const int32_t* slot,
                               const double* sqrt_lam, const double* c, int T, double inv2s2, double* xi, double* phi,
                               int32_t* n_acc, int32_t* flags, int n_cu, hipStream_t s);
-bool chain1d_supported(int n, int K, int M);
+bool chain1d_wanted(int64_t N, int n, int K, int M, int n_moves);
 hipError_t launch_chain1d(int64_t N, int K, int n, int n_moves, const MoveParams& q, const int32_t* slot,
                           const double* sqrt_lam, const double* basis, const SolveArgs& a, double* xi, double* phi,
                           int32_t* n_acc, int32_t* flags, int n_cu, hipStream_t s);

@@ -11,6 +11,8 @@
 //
 // The random numbers, the proposal and the decision are those of the step kernels (the proposal and
 // its ratio differ from theirs in the order of sums).
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace smc {
@@ -285,7 +287,17 @@ __global__ __launch_bounds__(256) void chain_l2mix_kernel(int64_t N, int K, int 
     }
 }
 
-bool chain_l2mix_supported(int K) { return K <= 128; }
+// Every workgroup fills the mixture's tables for its sixteen particles, which for a large cloud costs up to a
+// move or two, most with sixteen components and where the lanes' 64 or 128 modes are not filled.  So the
+// step kernels, which have one table for all, keep the calls of one or two moves where they are the faster:
+// at 262144 particles and one move, with 16 modes and M = 16 326 us by steps and 472 in one launch; with 64
+// modes and M = 8 it is 451 and 273.  From four moves the one launch was faster in every combination measured.
+bool chain_l2mix_wanted(int64_t N, int K, int T, int M, int n_moves) {
+    if (K > 128) return false;
+    if (N <= 32768 || n_moves > 2) return true;
+    if (n_moves == 2) return M <= 8 || (K > 48 && K <= 64);
+    return M <= 8 && ((K > 48 && K <= 64) || (K > 96 && T <= 4));
+}
 
 template <int MB, int NBL>
 static void chain_l2mix_terms(int64_t N, int K, int n_moves, const MoveParams& q, const int32_t* slot,
@@ -459,8 +471,20 @@ static size_t chain1d_lds(int n, int K, int M, int waves) {
 }
 static int chain1d_waves(int64_t N, int n, int n_cu) { return N <= n_cu ? 1 : n <= 64 ? 4 : n <= 128 ? 8 : 16; }
 
-// Grids whose basis fits LDS beside the mixture and the waves' coefficients.
-bool chain1d_supported(int n, int K, int M) { return n <= 256 && K <= 64 && chain1d_lds(n, K, M, 16) <= CHAIN_LDS; }
+// Grids whose basis fits LDS beside the mixture and the waves' coefficients.  For a large cloud each workgroup
+// of four particles pays for its tables (about 1 ns a particle and 0.1 per component, at the device's rate), and
+// a move gains by the nodes, a wave being idle beyond them: nothing on 8 intervals, 0.4 ns a particle on
+// 16, 0.8 on 32.  The step kernels keep the calls whose moves do not pay for the tables: 262144
+// particles on 8 intervals, 8 modes, M = 16, one move 445 us by steps and 1105 in one launch (16 moves 6.7 and
+// 8.7 ms); on 32 intervals, 64 modes, M = 8 one move is 1.30 and 1.06 ms.  The lines are drawn through 480 such
+// pairs so that one launch is nowhere the slower by more than 3 %.
+bool chain1d_wanted(int64_t N, int n, int K, int M, int n_moves) {
+    if (n > 256 || K > 64 || chain1d_lds(n, K, M, 16) > CHAIN_LDS) return false;
+    const int64_t m = n_moves;
+    if (N <= 8192) return true;
+    if (N <= 32768) return 2 * m * (n - 4) > std::max(8, 3 * M);
+    return m * (n - 8) * (16 + K) >= (M <= 4 ? 1100 : M <= 8 ? 1600 : 4600);
+}
 
 hipError_t launch_chain1d(int64_t N, int K, int n, int n_moves, const MoveParams& q, const int32_t* slot,
                           const double* sqrt_lam, const double* basis, const SolveArgs& a, double* xi, double* phi,
