@@ -172,3 +172,38 @@ def test_next_double_does_not_pass(N):
         assert step(phi, 1.0 - h) == (h, 1.0)
         above = np.nextafter(h, 1.0)
         assert step(phi, 1.0 - above)[0] < above
+
+
+@pytest.mark.parametrize("N", [4000, 8192, 8193, 100003, 1 << 20])
+@pytest.mark.parametrize("heavy", [1, 3, 200])
+def test_resample_few_heavy_particles(N, heavy):
+    """Particles with many outputs each, alone and beside particles with few, written by their wave: exact, and in a
+    time of the order of spread weights' (a thread by itself took a thousand times as long)."""
+    from paper_2503_16028_amd import smc
+    banner("resample heavy", N, heavy)
+    rng = np.random.default_rng(N + heavy)
+    W = inputs.weights(N, 5, "dirichlet") * 1e-2
+    at = rng.choice(N, heavy, replace=False)
+    at[0] = N // 2
+    W[at] += 0.99 * (1 - 1e-9) / heavy
+    u = inputs.u53(N)
+    idx = torch.empty(N, dtype=torch.int32, device=DEV)
+    smc.smc_resample(N, t(W), u, idx)
+    assert np.array_equal(idx.cpu().numpy(), np.array(systematic(W, u)))
+    spread = t(inputs.weights(N, 6, "dirichlet"))
+
+    def best(w):
+        out = np.inf
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        for _ in range(5):
+            a.record()
+            smc.smc_resample(N, w, u, idx)
+            b.record()
+            torch.cuda.synchronize()
+            out = min(out, a.elapsed_time(b))
+        return out
+
+    few, many = best(t(W)), best(spread)
+    print("   heavy %.3f ms, spread %.3f ms" % (few, many), flush=True)
+    # a wave writes 64 outputs at a time: at most N / 64 stores in a row, 10 ns each on their way to memory
+    assert few <= 2.0 * many + 0.02 + N / 64 * 1e-5
