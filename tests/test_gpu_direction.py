@@ -78,3 +78,36 @@ def test_iterations_on_rough_fields(n, prec, margin):
         o, q = obs.double().mean().item(), kept.double().mean().item()
         print("   ", o, q, flush=True)
         assert o <= (q + 1.0 if name == "smooth" else margin * q)
+
+
+@pytest.mark.parametrize("n,prec,buffers", [(256, 1, 10), (256, 0, 4), (128, 0, 4)])
+def test_directions_are_folded_within_a_sweep(n, prec, buffers):
+    """A sweep with more iterations than there are direction buffers (ten in FP32, four in FP64) folds them into the
+    correction on the way.  In FP32, which solves to 1e-3 a sweep, that takes a field without decay (of standard
+    deviation about a half), even with an inner tolerance out of reach: smooth fields take six.  The counters show that one did: more iterations than buffers times the sweeps that
+    iterated (each solve's last sweep only finds that it has converged).  Observations to 1e-9, as that solver's other
+    tests have them."""
+    from oracle.forward import observe, solve
+    from oracle.problem import Problem as OProblem, synthesize
+    from paper_2503_16028_amd import smc
+    print("[case] folded directions", n, prec, flush=True)
+    d = json.load(open(golden("problem_t2.json")))
+    at = [[1, 1], [n // 2, n // 2], [n - 1, n // 4], [n // 3, n - 1]]
+    d.update(grids=[n], obs_den=n, obs=at, y=[0.0] * 4, sigma=1.0)
+    op = OProblem(d)
+    N = 2
+    p = smc.Problem(d, N, tol_inner=1e-14 if prec else 1e-3, max_iter=2000)
+    x = inputs.particles(N, op.K, 64)
+    if prec:
+        k = np.arange(8.0) ** 2   # eight modes per axis
+        x *= (1 + np.pi ** 2 * (k[:, None] + k)).reshape(-1) / 16
+    G = torch.empty(N, 4, dtype=torch.float64, device=DEV)
+    smc.smc_profile(p, True)
+    smc.smc_forward_batch(p, N, torch.tensor(x, device=DEV), None, prec, G)
+    c = smc.smc_profile_read(p)
+    assert smc.smc_status_flags(p) == 0
+    print("   ", c, flush=True)
+    assert c["solves"] == N and c["iters"] > buffers * (c["sweeps"] - c["solves"])
+    for k in range(N):
+        ref = observe(op, solve(op, synthesize(op, x[k], n), n), n)
+        assert np.abs(G[k].cpu().numpy() - ref).max() <= 1e-9 * np.abs(ref).max()
