@@ -432,7 +432,9 @@ __device__ __noinline__ double strip_residual(const double* __restrict__ e_, con
     double xS = at_off<double>(xo, (own - (g0 > 0 ? NN : 0)) * 8u), xC = at_off<double>(xo, own * 8u);
     xS = (g0 > 0 && colin) ? xS : 0.0;
     xC = (g0 < NN - 1 && colin) ? xC : 0.0;
-    constexpr int B = R < 8 ? R : 8;   // rows whose loads are issued together
+    // rows whose loads are issued together: eight, or four where two workgroups share a compute unit (the
+    // forward problem in the 8-row shape, FP32: eight rows take 180 registers, and 3000 states 580 us, not 412)
+    constexpr int B = R < 8 ? R : (R == 8 && !SRC && std::is_same<T, float>::value) ? 4 : 8;
     static_assert(R % B == 0, "strip blocking");
 #pragma unroll 1
     for (int r0 = 0; r0 < R; r0 += B) {
@@ -1468,16 +1470,25 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
     __syncthreads();   // the next body may reuse the LDS
 }
 
-// Waves per SIMD a kernel's registers must leave room for: two workgroups per compute unit at 64^2
-// and below (FP32, observations only).
-template <typename T, int NN, int R, bool KEEP>
+// Whether a forward solve forms only its observations where no more is wanted.  Not in the 16-row shape at 128^2: in
+// the 128 registers of its four waves per SIMD that spills (260 bytes), and 3000 potentials take 3.02 ms where
+// the kernel that keeps the solution takes 2.28 (2.88 before either was reworked).
+template <int NN, int R, bool DST>
+constexpr bool onchip_obs_only() { return DST && !(NN == 128 && R == 16); }
+
+// Waves per SIMD a forward kernel's registers must leave room for (FP32): four at 32^2 and in the 8-row shape at
+// 64^2, two workgroups per compute unit there (without the bound 2048 observations at 32^2 by 8 rows take 97 us
+// instead of 81); two workgroups also in the 4-row shape where only observations are formed.
+template <typename T, int NN, int R, bool KEEP, bool ADJ = false>
 constexpr int onchip_waves() {
-    return (!KEEP && std::is_same<T, float>::value && NN <= 64 && R <= 8) ? cmax(1, 2 * NN * NN / R / 256) : 1;
+    if (!std::is_same<T, float>::value || ADJ) return 1;
+    if (NN == 32 || (NN == 64 && R == 8)) return 4;
+    return NN == 64 && R == 4 && !KEEP ? 8 : 1;
 }
 
 template <typename T, int NN, int R, bool DST, bool ADJ, bool AONLY = false, bool KEEP = true>
-__global__ __launch_bounds__(NN * NN / R, (onchip_waves<T, NN, R, KEEP>())) void cg_onchip(SolveArgs a, const _Float16* __restrict__ Stab,
-                                                         const float* __restrict__ lamtab) {
+__global__ __launch_bounds__(NN * NN / R, (onchip_waves<T, NN, R, KEEP, ADJ>())) void cg_onchip(
+    SolveArgs a, const _Float16* __restrict__ Stab, const float* __restrict__ lamtab) {
     __shared__ __align__(16) unsigned char smem[onchip_smem<T, NN, R, DST, KEEP>()];
     __shared__ SolveShared sh;
     cg_onchip_body<T, NN, R, DST, ADJ, true, AONLY, KEEP>(a, blockIdx.x, a.obs, smem, sh, Stab, lamtab);
@@ -1499,7 +1510,7 @@ constexpr int D256_BYTES = 256 * D256_LD * 2;
 // LDS named at module level: the mixed-grid solve's bodies and the 256^2 transform below are
 // functions of their own (register-allocated apart from their callers), and LDS they name directly
 // keeps its LDS instructions, where a pointer passed in would turn into generic accesses.
-constexpr int MIXED_SMEM = cmax(cmax(D256_BYTES, onchip_smem<float, 128, 16, true, false>()),
+constexpr int MIXED_SMEM = cmax(cmax(D256_BYTES, onchip_smem<float, 128, 32, true, false>()),
                                 cmax(onchip_smem<float, 64, 4, true, false>(), onchip_smem<double, 64, 4, false>()));
 __shared__ __align__(16) unsigned char g_mixed_smem[MIXED_SMEM];
 
@@ -2646,9 +2657,10 @@ __shared__ SolveShared g_mixed_sh;
 template <typename T, int NN, int R, bool DST, bool SE = true>
 __device__ __noinline__ void mixed_onchip(const SolveArgs& a, int64_t p, const int32_t* obs, const void* S,
                                           const float* lam) {
-    static_assert(onchip_smem<T, NN, R, DST, !DST>() <= MIXED_SMEM, "mixed-grid LDS");
-    cg_onchip_body<T, NN, R, DST, false, SE, false, !DST>(a, p, obs, g_mixed_smem, g_mixed_sh, reinterpret_cast<const _Float16*>(S),
-                                         lam);
+    constexpr bool KEEP = !onchip_obs_only<NN, R, DST>();
+    static_assert(onchip_smem<T, NN, R, DST, KEEP>() <= MIXED_SMEM, "mixed-grid LDS");
+    cg_onchip_body<T, NN, R, DST, false, SE, false, KEEP>(a, p, obs, g_mixed_smem, g_mixed_sh,
+                                                          reinterpret_cast<const _Float16*>(S), lam);
 }
 
 template <typename T>
@@ -2823,17 +2835,15 @@ __device__ __forceinline__ int64_t list_item(const unsigned long long* counters,
     return __builtin_amdgcn_readfirstlane(list[start + blockIdx.x]);
 }
 
-template <typename T, int NN, int R>
-__global__ __launch_bounds__(NN * NN / R, (onchip_waves<T, NN, R, false>())) void solve_list_onchip(SolveArgs a, const int32_t* __restrict__ list,
-                                                                 const unsigned long long* counters, int lvl,
-                                                                 const int32_t* __restrict__ obs,
-                                                                 const _Float16* __restrict__ Stab,
-                                                                 const float* __restrict__ lamtab) {
-    __shared__ __align__(16) unsigned char smem[onchip_smem<T, NN, R, true, false>()];
+template <typename T, int NN, int R, bool KEEP = !onchip_obs_only<NN, R, true>()>
+__global__ __launch_bounds__(NN * NN / R, (onchip_waves<T, NN, R, KEEP>())) void solve_list_onchip(
+    SolveArgs a, const int32_t* __restrict__ list, const unsigned long long* counters, int lvl,
+    const int32_t* __restrict__ obs, const _Float16* __restrict__ Stab, const float* __restrict__ lamtab) {
+    __shared__ __align__(16) unsigned char smem[onchip_smem<T, NN, R, true, KEEP>()];
     __shared__ SolveShared sh;
     const int64_t p = list_item(counters, lvl, list);
     if (p < 0) return;
-    cg_onchip_body<T, NN, R, true, false, true, false, false>(a, p, obs, smem, sh, Stab, lamtab);
+    cg_onchip_body<T, NN, R, true, false, true, false, KEEP>(a, p, obs, smem, sh, Stab, lamtab);
 }
 
 template <typename T, int NN>
@@ -2914,12 +2924,10 @@ hipError_t launch_solve_levels(int prec, int64_t N, const SolveArgs& a, const Le
 template <typename T, int NN, int R, bool DST>
 static hipError_t run_onchip(int64_t N, const SolveArgs& a, const void* S, const float* lam, hipStream_t s) {
     const _Float16* Sb = reinterpret_cast<const _Float16*>(S);
-    if (a.lam)
-        cg_onchip<T, NN, R, DST, true><<<dim3((unsigned)N), dim3(NN * NN / R), 0, s>>>(a, Sb, lam);
-    else if (DST && !a.keep)
-        cg_onchip<T, NN, R, DST, false, false, !DST><<<dim3((unsigned)N), dim3(NN * NN / R), 0, s>>>(a, Sb, lam);
-    else
-        cg_onchip<T, NN, R, DST, false><<<dim3((unsigned)N), dim3(NN * NN / R), 0, s>>>(a, Sb, lam);
+    const dim3 grid((unsigned)N), block(NN * NN / R);
+    if (a.lam) cg_onchip<T, NN, R, DST, true><<<grid, block, 0, s>>>(a, Sb, lam);
+    else if (a.keep) cg_onchip<T, NN, R, DST, false><<<grid, block, 0, s>>>(a, Sb, lam);
+    else cg_onchip<T, NN, R, DST, false, false, !onchip_obs_only<NN, R, DST>()><<<grid, block, 0, s>>>(a, Sb, lam);
     return hipGetLastError();
 }
 
