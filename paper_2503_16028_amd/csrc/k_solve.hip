@@ -275,6 +275,7 @@ struct SolveShared {
     double red1[16], red2[16];
     double src_w[MAX_OBS];   // adjoint point sources: weight and unknown index (-1: none)
     int src_at[MAX_OBS];
+    unsigned src_rows[8];    // of the global solver: the grid rows that hold one, a bit each (at most 256 rows)
 };
 
 // The FP64 passes over one thread's strip (column c, rows g0 .. g0 + R - 1).  They run outside the
@@ -1815,6 +1816,7 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
     auto interior = [&](int g, int c) { return c < NN - 1 && g < NN - 1; };
     int napp = 0;
 
+    if (ADJ && tid < 8) sh.src_rows[tid] = 0;   // read after the observation's barriers
     for (int k = tid; k < nodes; k += 1024) {
         const int g = k / NN, c = k % NN, i = c + 1, j = g + 1;
         double sdv = 1.0, tt = 0.0;
@@ -1843,6 +1845,7 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
             if (a.G) a.G[row * a.n_obs + tid] = val;
             src_w[tid] = 2.0 * a.inv2s2 * (val - a.y[tid]);
             src_at[tid] = in ? (jj - 1) * NN + ii - 1 : -1;
+            if (ADJ && in) atomicOr(&sh.src_rows[(jj - 1) >> 5], 1u << ((jj - 1) & 31));
         }
         if (tid < 64) {
             const double dlt = (tid < a.n_obs) ? val - a.y[tid] : 0.0;
@@ -1860,9 +1863,12 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
         const int pass = ADJ ? pass_ : 0;
         if (pass == 1 && first == 1) observe(true);
         double* xo = pass ? a.lam + row * a.lam_stride : x64;
-        auto rhs = [&](int flat) -> double {
+        // the sum over the sources only in the rows that hold one: at every node it was a tenth of an adjoint solve
+        // (gradients of 300 kept states at 256^2 in FP32 4.91 -> 4.45 ms)
+        auto rhs = [&](int flat, int g) -> double {
             if (pass == 0) return a.f;
             double s = 0.0;
+            if (!(sh.src_rows[g >> 5] >> (g & 31) & 1u)) return s;
             for (int k = 0; k < a.n_obs; ++k) s += (src_at[k] == flat) ? src_w[k] : 0.0;
             return s;
         };
@@ -1878,7 +1884,7 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
                 const int g = k / NN, c = k % NN, i = c + 1, j = g + 1;
                 T rk = T(0);
                 if (interior(g, c)) {
-                    double res = rhs(k);
+                    double res = rhs(k, g);
                     if (sweep > 0) {
                         const double xP = xo[k];
                         const double xE = (c + 1 < NN - 1) ? xo[k + 1] : 0.0;
