@@ -570,7 +570,7 @@ static hipError_t forward_levels(smc_problem_s* ps, int prec, int64_t N, const d
     if (dst) {   // one launch per grid, each in its single-grid shape
         int rows[MAX_LEVELS] = {};
         for (int l = 0; l < P.n_levels; ++l) rows[l] = P.lv[l].rows;
-        e = launch_solve_levels(prec, N, a, lt, rows, P.ws_list, P.ws_counters, P.n_cu, s);
+        e = launch_solve_levels(prec, N, a, lt, rows, P.ws_list, P.ws_counters, s);
     } else {
         e = launch_solve_mixed(prec, N, a, lt, o.level, P.ws_list, P.ws_counters, P.n_cu, s);
     }
@@ -793,8 +793,8 @@ static int move_loop(smc_problem_s* p, int64_t N, MoveParams q, int32_t n_moves,
         chain1d_wanted(N, P.lv[0].n, P.K, q.M, n_moves)) {
         const bool rec = P.profiling && !p->capturing;
         if (rec) HIPCHK(record(p->pool, s));
-        HIPCHK(launch_chain1d(N, P.K, P.lv[0].n, n_moves, q, P.slot, P.sqrt_lam, P.lv[0].basis, solve_args(P, 0), xi, phi,
-                              n_acc, P.flags, P.n_cu, s));
+        HIPCHK(launch_chain1d(N, P.K, P.lv[0].n, n_moves, q, P.slot, P.sqrt_lam, P.lv[0].basis, solve_args(P, 0), xi,
+                              phi, n_acc, P.flags, P.n_cu, s));
         if (rec) HIPCHK(record(p->pool, s, n_moves));
         return SMC_OK;
     }

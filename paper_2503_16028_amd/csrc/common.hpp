@@ -51,7 +51,7 @@ struct Problem {
     int32_t active_h[MAX_KR];
     double* y = nullptr;         // [n_obs]
     // workspace, all for n_max particles
-    double* ws_v = nullptr;      // [n_max][K]    proposals; during a fit [workgroups of 64 particles][kr][64], its tiles
+    double* ws_v = nullptr;      // [n_max][K]    proposals; during a fit its tiles, [groups of 64 particles][kr][64]
     double* ws_logr = nullptr;   // [n_max]       log R of the proposal
     double* ws_phinew = nullptr; // [n_max]       potential of the proposal
     double* ws_e = nullptr;      // [n_max][(n_big+1)^dim]  exp(u/2) at the nodes
@@ -306,7 +306,7 @@ hipError_t launch_plan(int64_t N, const int32_t* level, const LevelTable& lt, in
 // grid's single-grid launch (rows[l]: its tile, 0 = default), after launch_plan: FP32 with FP64
 // refinement or FP64, fast-Poisson preconditioners on every grid.
 hipError_t launch_solve_levels(int prec, int64_t N, const SolveArgs& a, const LevelTable& lt, const int* rows,
-                               const int32_t* list, unsigned long long* counters, int n_cu, hipStream_t s);
+                               const int32_t* list, unsigned long long* counters, hipStream_t s);
 // The solves of a level map without the fast-Poisson preconditioner, in one persistent launch.
 hipError_t launch_solve_mixed(int prec, int64_t N, const SolveArgs& a, const LevelTable& lt, const int32_t* level,
                               const int32_t* list, unsigned long long* counters, int grid, hipStream_t s);

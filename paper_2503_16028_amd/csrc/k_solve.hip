@@ -201,7 +201,8 @@ __device__ __forceinline__ void dst_apply(const T (&rin)[R], double rr, unsigned
     // Z[g][c] = sum_l T3[g][l] S[l][c], for rows as (S T3^T)[c][g]
     product(bufB, std::integral_constant<bool, !COLS>{}, [&](int tile, int q, f4 acc) __attribute__((always_inline)) {
         const int strip = (sg * SP + q) * 16;
-        *reinterpret_cast<float4*>(Z + (COLS ? (strip + lr) * LDZ + tile * 16 : (tile * 16 + lr) * LDZ + strip) + 4 * lk) =
+        const int at = COLS ? (strip + lr) * LDZ + tile * 16 : (tile * 16 + lr) * LDZ + strip;
+        *reinterpret_cast<float4*>(Z + at + 4 * lk) =
             make_float4(acc[0] * unsc, acc[1] * unsc, acc[2] * unsc, acc[3] * unsc);
     });
     __syncthreads();
@@ -467,7 +468,8 @@ __device__ __noinline__ double strip_residual(const double* __restrict__ e_, con
             const double xw = (c > 0) ? xw_ : 0.0;
             const bool in = colin && g < NN - 1;
             const double fr = rhs_at(r);
-            const double res = fr - eC * inv_h2 * (eE * (xC - xe) + eW * (xC - xw) + eN[k] * (xC - xn) + eS * (xC - xS));
+            const double res =
+                fr - eC * inv_h2 * (eE * (xC - xe) + eW * (xC - xw) + eN[k] * (xC - xn) + eS * (xC - xS));
             acc += in ? res * res : 0.0;
             tb[NN + 1 + r * NN] = in ? (T)(sdv[k] * res) : T(0);
             eS = eC;
@@ -505,9 +507,13 @@ __device__ __noinline__ void strip_update(double* xo_, const SD* sd_, const T* t
 // solution y in the strip's LDS slots, the correction dx = D^{-1/2} y is rounded to T and staged, the
 // FP64 residual in `rb` is updated, r <- r - A dx (r = f before the first step), and the scaled
 // residual D^{-1/2} r goes to the strip's `out` slots (an LDS array of its own: other waves still read
-// dx).  Returns the strip's share of |r|^2.  The iterate itself is never formed: dx is exact as stored, the update evaluates
-// the same FP64 operator as strip_residual, so r = f - A (sum of dx) up to FP64 rounding, and each
-// observation is the FP64 sum of its node's corrections (g_src_at: the nodes, g_src_w: the sums).
+// dx).  Returns the strip's share of |r|^2.  The iterate itself is never formed: dx is exact as stored, the
+// update evaluates the same FP64 operator as strip_residual, so r = f - A (sum of dx) up to FP64 rounding, and
+// each observation is the FP64 sum of its node's corrections (g_src_at: the nodes, g_src_w: the sums).  The
+// rounding of dx moves no error into the observations: it is part of the next residual, as the rounding of y to T
+// is in strip_update's FP64 product.  Against 64-bit solves of 256 fields the mean error at 64^2 in FP32 is
+// 4.4e-13 either way, 2.2e-12 with three times the prior's spread; at 128^2 3.7e-13 and 3.1e-13 (2.4e-12 and
+// 1.6e-12), where the first direction also differs: what is left of a residual of at most 1e-10.
 // Bound by its memory instructions and the chain from loads to stores: per node and step it reads e, r
 // and D^{-1/2} and writes r, where a separate iterate read and wrote x, read it again with its
 // neighbours, and passed twice; the neighbours of dx are LDS words at immediate offsets.  Measured with
@@ -603,8 +609,8 @@ __device__ __forceinline__ double strip_refine(const double* __restrict__ e_, do
 
 // The same step at 128^2 with the nodes dealt out anew: a thread takes two columns of a band of rows, a wave
 // whole rows.  The strips' way costs some 50 instructions a node, which with two waves per SIMD is
-// what a step takes; in pairs the loads and stores are twice as wide, half of the horizontal neighbours are the thread's
-// own, a row's address and its place in the grid are scalars, and D^{-1/2} is read once.  NT threads.
+// what a step takes; in pairs the loads and stores are twice as wide, half of the horizontal neighbours are
+// the thread's own, a row's address and its place in the grid are scalars, and D^{-1/2} is read once.  NT threads.
 // The inner solution y is in the LDS slots of its strips.  Four rows at a time (two 1.73, eight spill: 1.79 ms) and
 // without loads ahead of a block (they spill: 1.88).  4096 potentials 1.82 -> 1.71 ms, of 8 particles 105 -> 95 us.
 template <typename T, int NN, int NT, typename SD, bool SE>
@@ -693,7 +699,7 @@ __device__ __noinline__ double pair_refine(const double* __restrict__ e_, double
             res[1] = row && lane < 63 ? res[1] : 0.0;
             acc += res[0] * res[0];
             acc += res[1] * res[1];
-            asm volatile("" : "+v"(acc), "+v"(res)::"memory");   // a row at a time: the compiler would hold many, and spill
+            asm volatile("" : "+v"(acc), "+v"(res)::"memory");   // a row at a time: the compiler would hold many
             put_off<D2U>(rb + r * NN * 8, ro_, res);
             T2 o;
             o[0] = (T)((double)sv[r][0] * res[0]);
@@ -867,8 +873,10 @@ __device__ __noinline__ double pair_residual(const double* __restrict__ e_, cons
             D2U xn;
             xn[0] = above ? xN[k][0] : 0.0;
             xn[1] = above && !last ? xN[k][1] : 0.0;
-            const double flux0 = eC[1] * (xC[0] - xC[1]) + eW * (xC[0] - xw) + eN[k][0] * (xC[0] - xn[0]) + eS[0] * (xC[0] - xS[0]);
-            const double flux1 = eE * (xC[1] - xe) + eC[0] * (xC[1] - xC[0]) + eN[k][1] * (xC[1] - xn[1]) + eS[1] * (xC[1] - xS[1]);
+            const double flux0 =
+                eC[1] * (xC[0] - xC[1]) + eW * (xC[0] - xw) + eN[k][0] * (xC[0] - xn[0]) + eS[0] * (xC[0] - xS[0]);
+            const double flux1 =
+                eE * (xC[1] - xe) + eC[0] * (xC[1] - xC[0]) + eN[k][1] * (xC[1] - xn[1]) + eS[1] * (xC[1] - xS[1]);
             double r0_ = f - eC[0] * inv_h2 * flux0, r1_ = f - eC[1] * inv_h2 * flux1;
             r0_ = row ? r0_ : 0.0;
             r1_ = row && !last ? r1_ : 0.0;
@@ -975,7 +983,8 @@ __device__ __forceinline__ void strip_setup(const double* __restrict__ e_, SD* _
 // after a barrier); FIRST: with the first scaled residual D^{-1/2} f into `out`, which saves strip_first its
 // pass.  4096 potentials 1.72 -> 1.61 ms, of 8 particles 95 -> 90 us.
 template <typename T, int NN, int NT, typename SD, bool SE, bool FIRST>
-__device__ __noinline__ void pair_setup(const double* __restrict__ e_, SD* __restrict__ sd_, T* ly_, T* out_, double f) {
+__device__ __noinline__ void pair_setup(const double* __restrict__ e_, SD* __restrict__ sd_, T* ly_, T* out_,
+                                        double f) {
     static_assert(NN == 128, "a row is 64 pairs");
     constexpr int NP1 = NN + 1, PAD = NN + 1, RB = NN * NN / 2 / NT, B = RB < 8 ? RB : 8;
     typedef T T2 __attribute__((ext_vector_type(2)));
@@ -1226,9 +1235,9 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
             if constexpr (!KEEP) {   // the residual: f at first, then as the last step left it
                 if (sweep == 0) {
                     rr64 = a.f * a.f * (double)((NN - 1) * (NN - 1));
-                    if constexpr (NN == 128) {}   // the setup left it
-                    else if constexpr (WIDE) strip_first_call<T, NN, R, SD>(sd, lout, c, b * R, a.f);
-                    else strip_first<T, NN, R, SD>(sd, lout, c, b * R, a.f);
+                    if constexpr (NN != 128 && WIDE) strip_first_call<T, NN, R, SD>(sd, lout, c, b * R, a.f);
+                    else if constexpr (NN != 128) strip_first<T, NN, R, SD>(sd, lout, c, b * R, a.f);
+                    // at 128^2 the setup left it
                 }
             } else if constexpr (SPLIT) {
                 bool pairs = false;
@@ -1237,10 +1246,10 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
                     if (pairs) acc = pair_residual<T, NN, NT, SD, SE>(e, xo, sd, ly, a.f);
                 }
                 if (!pairs)
-                acc = (pass == 1) ? strip_residual<T, NN, R, true, SD, SE>(e, xo, sd, tb, c, b * R, sweep == 0, a.f, src_w,
-                                                                   src_at, a.n_obs)
-                                  : strip_residual<T, NN, R, false, SD, SE>(e, xo, sd, tb, c, b * R, sweep == 0, a.f, src_w,
-                                                                    src_at, a.n_obs);
+                    acc = (pass == 1) ? strip_residual<T, NN, R, true, SD, SE>(e, xo, sd, tb, c, b * R, sweep == 0, a.f,
+                                                                               src_w, src_at, a.n_obs)
+                                      : strip_residual<T, NN, R, false, SD, SE>(e, xo, sd, tb, c, b * R, sweep == 0, a.f,
+                                                                                src_w, src_at, a.n_obs);
             } else
             if (sweep == 0) {
 #pragma unroll 1
@@ -1453,8 +1462,9 @@ __device__ __forceinline__ void cg_onchip_body(const SolveArgs& a, const int64_t
         ++solves;
         if (pass == 0) observe(ok);
     }
-    if constexpr (ADJ && NN >= 64) {   // dPhi/du from the final w and lam (the barrier closing the last sweep made them whole)
-        if (a.du && ok) strip_dphi<NN, R, AONLY>(e, x64, a.lam + row * a.lam_stride, a.du + row * a.du_stride, c, b * R);
+    if constexpr (ADJ && NN >= 64) {   // dPhi/du from the final w and lam (whole since the last sweep's barrier)
+        if (a.du && ok)
+            strip_dphi<NN, R, AONLY>(e, x64, a.lam + row * a.lam_stride, a.du + row * a.du_stride, c, b * R);
     }
 
     // ---- bookkeeping
@@ -1623,16 +1633,16 @@ __device__ __forceinline__ vec4_t<T> fma4(T a, vec4_t<T> b, vec4_t<T> c) {
 
 // The transform that ends in the next search direction, p = z + (r.z / rz) pc (p = z without pc), and
 // returns r.z.  With S symmetric, r.z = r.S (S r S) / lam S is the sum of (S r S)^2 / lam over the
-// modes, known half way, in FP32 from the matrix units' accumulators: the residual is not read again, and z, with beta in
-// hand before its last product, is neither written nor read.  That sum says nothing of an overflow in FP16 after it:
+// modes, known half way, in FP32 from the matrix units' accumulators: the residual is not read again, and z, with
+// beta in hand before its last product, is neither written nor read.  That sum says nothing of an overflow in FP16 after it:
 // call dstg_next, which looks at the staged scale first.
 // Inlined (a call saves a third of the registers to memory), with the thread's index opaque, so that no
 // address of it is kept through the loop over the iterations.
 __shared__ double g_dst_red[16];
 __shared__ __align__(16) float g_dst_lam[256];   // lam, staged by the kernel
 template <int NN, typename T>
-__device__ __forceinline__ double dstg_direction(const T* r, T* p, const T* pc, double rz, const _Float16* S, int staged,
-                                                 int ex) {
+__device__ __forceinline__ double dstg_direction(const T* r, T* p, const T* pc, double rz, const _Float16* S,
+                                                 int staged, int ex) {
     typedef T V4 __attribute__((ext_vector_type(4)));
     constexpr int LD = NN + 8, KS = NN / 32, NBT = NN / 16, WPC = 16 / NBT, RT = NBT / WPC;
     _Float16* X = reinterpret_cast<_Float16*>(g_mixed_smem);
@@ -1725,9 +1735,9 @@ __device__ __forceinline__ double dstg_direction(const T* r, T* p, const T* pc, 
 }
 
 // The direction of the residual r, rr = |r|^2.  `staged`: X holds it at the scale 2^-ex of its norm before the
-// update.  S being orthonormal, every intermediate is bounded by the staged norm, and by it over 2 lam_0 once divided by the
-// eigenvalues; where that bound leaves FP16 (65504, with a factor of two for its rounding: a residual that has
-// grown some 20-fold at 256^2, 80-fold at 128^2, since its scale was taken) r is staged anew from memory.
+// update.  S being orthonormal, every intermediate is bounded by the staged norm, and by it over 2 lam_0 once
+// divided by the eigenvalues; where that bound leaves FP16 (65504, with a factor of two for its rounding: a
+// residual that has grown some 20-fold at 256^2, 80-fold at 128^2, since its scale was taken) r is staged anew.
 template <int NN, typename T>
 __device__ __forceinline__ double dstg_next(const T* r, T* p, const T* pc, double rz, const _Float16* S, int staged,
                                             int& ex, double rr) {
@@ -2266,8 +2276,9 @@ __device__ __forceinline__ double lane_before(double v) { return from_prev_lane(
 __device__ __forceinline__ double lane_after(double v) { return from_next_lane(v, 0.0); }
 
 template <typename T, int NN>
-__device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int64_t row, const int32_t* __restrict__ obs,
-                                                   SolveShared& sh, _Float16* X, const _Float16* __restrict__ Stab,
+__device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int64_t row,
+                                                   const int32_t* __restrict__ obs, SolveShared& sh, _Float16* X,
+                                                   const _Float16* __restrict__ Stab,
                                                    const float* __restrict__ lamtab) {
     constexpr int NW = 16, nodes = NN * NN, NP1 = NN + 1, R = nodes / 1024;
     constexpr bool F32 = GlobalSlots<T, NN>::F32, W0 = F32 && NN >= DST_W0_MIN;
@@ -2330,7 +2341,8 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
         int ex = norm_exponent(rr) + 3;   // the scale of X
         // x <- x + sum of the np directions, taken into x
         auto direction = [&](int k) -> const T* {
-            if constexpr (W0) return (sweep == 0 && !have_x && k == 0) ? reinterpret_cast<const T*>(w0) : pb + k * nodes;
+            if constexpr (W0)
+                if (sweep == 0 && !have_x && k == 0) return reinterpret_cast<const T*>(w0);
             return pb + k * nodes;
         };
         auto correction = [&](int k4) -> T4 {
@@ -2879,8 +2891,7 @@ __global__ __launch_bounds__(256) void reject_list_kernel(SolveArgs a, const int
 }
 
 hipError_t launch_solve_levels(int prec, int64_t N, const SolveArgs& a, const LevelTable& lt, const int* rows,
-                               const int32_t* list, unsigned long long* counters, int n_cu, hipStream_t s) {
-    (void)n_cu;
+                               const int32_t* list, unsigned long long* counters, hipStream_t s) {
     if (N <= 0) return hipSuccess;
     int order[MAX_LEVELS];   // finest grid first, as the list is
     for (int l = 0; l < lt.n_levels; ++l) order[l] = l;
@@ -2889,7 +2900,7 @@ hipError_t launch_solve_levels(int prec, int64_t N, const SolveArgs& a, const Le
             if (lt.n[order[j]] > lt.n[order[i]]) std::swap(order[i], order[j]);
     SolveArgs b = a;
     if (prec == SMC_FP64) b.tol_inner = 0.1 * a.tol64;   // FP64 CG to 0.1 tol64 in one sweep, as single-grid
-    const dim3 g1((unsigned)N), g4((unsigned)N);   // at most N particles per grid
+    const dim3 g1((unsigned)N);   // at most N particles per grid
     for (int k = 0; k < lt.n_levels; ++k) {
         const int l = order[k], n = lt.n[l];
         const _Float16* S = reinterpret_cast<const _Float16*>(lt.S[l]);
@@ -2903,11 +2914,11 @@ hipError_t launch_solve_levels(int prec, int64_t N, const SolveArgs& a, const Le
             else if (n == 128)
                 solve_list_onchip<float, 128, 32><<<g1, dim3(512), 0, s>>>(b, list, counters, l, obs, S, lam);
             else if (n == 64 && rows[l] == 4)
-                solve_list_onchip<float, 64, 4><<<g4, dim3(1024), 0, s>>>(b, list, counters, l, obs, S, lam);
+                solve_list_onchip<float, 64, 4><<<g1, dim3(1024), 0, s>>>(b, list, counters, l, obs, S, lam);
             else if (n == 64 && rows[l] == 16)
-                solve_list_onchip<float, 64, 16><<<g4, dim3(256), 0, s>>>(b, list, counters, l, obs, S, lam);
+                solve_list_onchip<float, 64, 16><<<g1, dim3(256), 0, s>>>(b, list, counters, l, obs, S, lam);
             else if (n == 64)
-                solve_list_onchip<float, 64, 8><<<g4, dim3(512), 0, s>>>(b, list, counters, l, obs, S, lam);
+                solve_list_onchip<float, 64, 8><<<g1, dim3(512), 0, s>>>(b, list, counters, l, obs, S, lam);
             else
                 return hipErrorInvalidValue;
         } else {
@@ -2916,7 +2927,7 @@ hipError_t launch_solve_levels(int prec, int64_t N, const SolveArgs& a, const Le
             else if (n == 128)
                 solve_list_global<double, 128><<<g1, dim3(1024), 0, s>>>(b, list, counters, l, obs, S, lam);
             else if (n == 64)
-                solve_list_onchip<double, 64, 8><<<g4, dim3(512), 0, s>>>(b, list, counters, l, obs, S, lam);
+                solve_list_onchip<double, 64, 8><<<g1, dim3(512), 0, s>>>(b, list, counters, l, obs, S, lam);
             else
                 return hipErrorInvalidValue;
         }

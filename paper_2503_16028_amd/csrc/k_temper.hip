@@ -99,8 +99,8 @@ __device__ __forceinline__ void add_point(Sums& e, double p, double pmin, double
 }
 // Entries beg, beg + step, ... of p.
 template <bool FIRST>
-__device__ __forceinline__ Sums add_points(const double* __restrict__ p, int64_t beg, int64_t N, int64_t step, double pmin,
-                                           double x) {
+__device__ __forceinline__ Sums add_points(const double* __restrict__ p, int64_t beg, int64_t N, int64_t step,
+                                           double pmin, double x) {
     Sums e{};
     int64_t k = beg;
     for (; k + 3 * step < N; k += 4 * step) {
