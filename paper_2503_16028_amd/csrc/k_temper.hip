@@ -207,16 +207,18 @@ __global__ __launch_bounds__(NT) void temper_kernel(int64_t N, const double* __r
     if (tid == 0) temper_scalars(t, N, h_out, tau_out, log_z, flags);
 }
 
-// Many workgroups: the chain min, first pass, PASSES Newton passes (those after the end of the search
+// Many workgroups: the chain min, first pass, Newton passes (those after the end of the search
 // return at once), a finish by one workgroup in case the search is still open, the weights.  State
 // and partial sums live in the first SCRATCH entries of W, in two copies that alternate between
 // launches; a last one-workgroup launch writes the weights of those entries.  A single workgroup
 // takes 1M particles through a pass in 0.7 ms, one compute unit's rate of FP64 exponentials; the whole
-// chain takes 114 us there (8.6 ms with one workgroup), of which 85, its time at 8065 particles, are launches and
+// chain takes 122 us there (8.6 ms with one workgroup), of which 85, its time at 8065 particles, are launches and
 // the latency of the sums.
 constexpr int TEMPER_BLOCKS = 256, STATE = 16;
 constexpr int SCRATCH = 2 * (STATE + 5 * TEMPER_BLOCKS);
-constexpr int PASSES = 16;   // about 11 for chi^2 potentials, up to 15 in nineteen clouds of twenty
+// Newton passes launched: 8 to 15 are taken for chi^2 potentials, up to 19 for spreads of ten decades.  One more costs
+// an idle launch, 2.4 us; one too few a pass by one workgroup, 40 us at 65536 particles and 0.7 ms at 2^20.
+static int temper_passes(int64_t N) { return N <= 65536 ? 16 : 20; }
 static_assert(SCRATCH <= TEMPER_ONE && sizeof(Temper) <= STATE * sizeof(double), "the scratch fits W");
 
 namespace {
@@ -339,7 +341,7 @@ hipError_t launch_temper(int64_t N, const double* phi, const double* tau_in, dou
     int par = 0;
     temper_min_kernel<<<grid, block, 0, s>>>(N, phi, W);
     temper_pass_kernel<true><<<grid, block, 0, s>>>(N, phi, tau_in, goal, W, par);
-    for (int i = 0; i < PASSES; ++i)
+    for (int i = 0; i < temper_passes(N); ++i)
         temper_pass_kernel<false><<<grid, block, 0, s>>>(N, phi, tau_in, goal, W, par ^= 1);
     temper_finish_kernel<<<dim3(1), dim3(1024), 0, s>>>(N, phi, goal, W, par ^= 1, blocks, h, tau_new, log_z, flags);
     par ^= 1;
