@@ -2119,14 +2119,14 @@ __device__ __forceinline__ void cg_global_body(const SolveArgs& a, const int64_t
 //     same nodes);
 //   - runs down bands of rows, the neighbours above and below carried in registers, the horizontal ones taken
 //     from the adjacent lanes;
-// and moves p twice, r twice, t and the direction before: 6 vector passes (FP64: 7, r once more), where
-// cg_global_body has 13 and a version with z and q in memory 10.
+// and moves p twice, r twice, t and the direction before: 6 vector passes (FP64 at 256^2, with q in memory and r
+// read twice, 9), where cg_global_body has 13 and a version with z and q in memory 10.
 // A refinement step rounds dx = D^{-1/2} y to T and updates the FP64 residual, as strip_refine does; the
 // FP64 passes run down columns, the vertical neighbours carried in registers.  The passes over the
 // vectors keep a few loads in flight per thread and leave the rest to the sixteen waves: unrolled
 // further they spill, and scratch traffic is what this solver can least afford.  Measured, with 13, 10 and
-// 6 (7) passes: 1024 solves at 256^2 in FP32 10.70, 7.73 and 5.5 ms; 32 solves 1.45, 0.93 and
-// 0.79; 1001 at 128^2 in FP64 2.77, 2.63 and 2.08.
+// 6 passes: 1024 solves at 256^2 in FP32 10.70, 7.73 and 5.3 ms; 32 solves 1.45, 0.93 and
+// 0.78; 1001 at 128^2 in FP64 2.77, 2.63 and 1.94.
 // Vector slots of a particle's row of a.vec (7 n^2 doubles): t, r, q, then the directions; FP32 has
 // the last one for x, FP64 keeps x in a.aux.
 template <typename T, int NN>
@@ -2289,6 +2289,7 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
     // the iteration's share of a thread: four columns from cc, a band of RB rows from g0
     constexpr int RB = nodes / 4096;
     constexpr bool QREG = RB * 4 * sizeof(T) <= 256;   // q in registers (not FP64 at 256^2)
+    constexpr bool RREG = QREG && !F32;                 // r too, from the product with A on (FP64 at 128^2)
     constexpr int QU = QREG ? RB : 2;
     constexpr uint32_t ROW = NN * sizeof(T);
     typedef T V4 __attribute__((ext_vector_type(4)));
@@ -2402,7 +2403,7 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
             }
             ex = norm_exponent(rr) + 3;
             const T sc = (T)ldexpf(1.0f, -ex);
-            V4 q[QREG ? RB : 1];
+            V4 q[QREG ? RB : 1], rk[RREG ? RB : 1];
             T pq_acc = T(0);
             double rp_acc = 0.0;
             {
@@ -2442,14 +2443,16 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
                     if constexpr (!F32) asm volatile("" : "+v"(rp_acc)::"memory");
                     if constexpr (QREG) q[i] = qi;
                     else put_off<V4>(qB, at, qi);
+                    if constexpr (RREG) rk[i] = r4;
                     at += ROW;
                 }
             }
             // In FP64 the step length takes r.p from the vectors: the transform's r.z, of operands in FP16,
             // would make each line search inexact, and one sweep runs to 1e-11.  On fields without decay
-            // (545 iterations at 128^2 with r.z from z) the solve took 597 without this and takes 556, for a
-            // seventh pass (1001 solves at 128^2 1.91 -> 2.08 ms).  In FP32, to 1e-3 a sweep, it
-            // changes nothing (805 and 811 iterations at 256^2).
+            // (545 iterations at 128^2 with r.z from z) the solve took 597 without this and takes 556.  At 128^2 r
+            // then stays in registers up to its update (1001 solves 1.90 -> 1.94 ms; read twice 2.13), at
+            // 256^2 it is read twice (256 solves 2.88 -> 3.01).  In FP32, to 1e-3 a sweep, it changes nothing
+            // (805 and 811 iterations at 256^2).
             double rp = rz;
             if constexpr (!F32) rp = block_sum<NW>(rp_acc, red2);
             pq = block_sum<NW>((double)pq_acc, red1);
@@ -2467,7 +2470,9 @@ __device__ __forceinline__ void cg_global_obs_body(const SolveArgs& a, const int
                 _Float16* xs = X + g0 * (NN + 8) + cc;
 #pragma unroll QU
                 for (int i = 0; i < RB; ++i) {
-                    V4 r4 = at_off<V4>(rB, at), q4;
+                    V4 r4, q4;
+                    if constexpr (RREG) r4 = rk[i];
+                    else r4 = at_off<V4>(rB, at);
                     if constexpr (QREG) q4 = q[i];
                     else q4 = at_off<V4>(qB, at);
                     r4 -= alpha * q4;
