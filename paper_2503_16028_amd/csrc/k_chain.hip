@@ -476,7 +476,7 @@ static int chain1d_waves(int64_t N, int n, int n_cu) { return N <= n_cu ? 1 : n 
 // a move gains by the nodes, a wave being idle beyond them: nothing on 8 intervals, 0.4 ns a particle on
 // 16, 0.8 on 32.  The step kernels keep the calls whose moves do not pay for the tables: 262144
 // particles on 8 intervals, 8 modes, M = 16, one move 445 us by steps and 1105 in one launch (16 moves 6.7 and
-// 8.7 ms); on 32 intervals, 64 modes, M = 8 one move is 1.30 and 1.06 ms.  The lines are drawn through 480 such
+// 8.7 ms); on 32 intervals, 64 modes, M = 8 one move is 1.30 and 1.06 ms.  The lines are drawn through 1440 such
 // pairs so that one launch is nowhere the slower by more than 3 %.
 bool chain1d_wanted(int64_t N, int n, int K, int M, int n_moves) {
     if (n > 256 || K > 64 || chain1d_lds(n, K, M, 16) > CHAIN_LDS) return false;
